@@ -11,21 +11,21 @@
 // transmission chord (Eq. 44) or the emission sweep (Eq. 45), and the bin's
 // spectrum is the g-weighted sum.
 //
-// k_ck_mix: one wave per (sample, layer) and a run of 16 bins, eight bins at a time,
-//   one per group of eight lanes.  Lane p of a group interpolates every absorber at
-//   g-point p (FP32 table entries relative to per-(absorber, column) offsets,
-//   bilinear in (T, log p), exp2 with the layer prefactor).  A merge gives lane p row
-//   p of the 8 x 8 pair matrix, mixture point p with each absorber point, which
-//   ascends because both distributions do; the 64 pair sums are sorted by the three
-//   merge levels of a bitonic network (DPP lane moves inside the group and
-//   compare-exchanges inside a lane; keys = the value's bits above the low six, the
-//   pair index in the low six), the exact sums and weights are looked up by index, and
-//   the integral of the sorted distribution over each g-interval comes from each
-//   element's overlap with it, in FP64, reduce-scattered over the group so that lane p
-//   receives its own interval.  Output: the mixed layer optical depths
-//   [B][L_pad][n_bins_pad x 8] (FP32), read by k_ck_trans (bf16x3 MFMA chord, as the
-//   cross-section path) or k_ck_emis (one lane per (bin, g-point) column sweeping up
-//   the layers).
+// k_ck_mix: one wave per (sample, layer, 16 bins), a quad of lanes per bin.  Lane q of a
+//   quad holds g-points 2q and 2q + 1: it interpolates every absorber there (FP32
+//   table entries relative to per-(absorber, column) offsets, bilinear in (T, log p),
+//   exp2 with the layer prefactor) and, in a merge, holds rows 2q and 2q + 1 of the
+//   8 x 8 pair matrix, each mixture point with every absorber point, which ascend
+//   because both distributions do.  The 64 pair sums are sorted by three merge levels:
+//   the lane's two rows (an odd-even merge of registers), then two lanes, then the quad
+//   (bitonic, quad_perm moves between lanes); keys = the value's bits above the low
+//   six, the pair index in the low six.  The exact sums and weights are looked up by
+//   index, their running sums (weights U, weights x values I, FP64) go to LDS in sorted
+//   order, and each lane finds its two g-interval edges there by bisection: the integral
+//   of the sorted distribution up to an edge E inside element r is I_r + v_r (E - U_r).
+//   Output: the mixed layer optical depths [B][L_pad][n_bins_pad x 8] (FP32), read by
+//   k_ck_trans (bf16x3 MFMA chord, as the cross-section path) or k_ck_emis (one lane per
+//   (bin, g-point) column sweeping up the layers).
 #include "ck.h"
 #include "emission.h"
 #include "kernels.h"
@@ -33,59 +33,26 @@
 
 namespace exofwd {
 
-// DPP lane moves inside 8-lane groups (gfx9 encodings): quad_perm patterns and the
-// half-row (8-lane) mirror
-constexpr int kDppXor1 = 0xB1;     // quad_perm [1,0,3,2]
-constexpr int kDppXor2 = 0x4E;     // quad_perm [2,3,0,1]
-constexpr int kDppQuadMirror = 0x1B;   // quad_perm [3,2,1,0]
-constexpr int kDppHalfMirror = 0x141;  // row_half_mirror: lane p <-> 7 - p of each 8
-constexpr int kDppShr1 = 0x111, kDppShr2 = 0x112, kDppShr4 = 0x114;   // row_shr:1, 2, 4
+// two adjacent FP32 table entries (8 bytes) through a buffer resource
+__device__ inline float2 load_f32x2(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
+  const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0);
+  return make_float2(__uint_as_float(v[0]), __uint_as_float(v[1]));
+}
+
+// DPP lane moves inside a quad (gfx9 quad_perm encodings)
+constexpr int kDppXor1 = 0xB1;         // [1,0,3,2]
+constexpr int kDppQuadMirror = 0x1B;   // [3,2,1,0]
+constexpr int kDppQuadPrev = 0x90;     // [0,0,1,2]
+constexpr int dpp_quad_lane(int j) { return j * 0x55; }   // lane j of the quad to all four
 
 template <int CTRL>
 __device__ inline uint32_t dpp_u(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, true);
 }
-
-// One cross-lane step of the sorting network: register r meets the partner lane's
-// register r (or 7 - r with `rev`); the lower lane of the pair keeps the smaller key.
-template <int CTRL, bool REV>
-__device__ inline void net_cross(uint32_t (&k)[8], bool lower) {
-  uint32_t o[8];
-#pragma unroll
-  for (int r = 0; r < 8; ++r) o[r] = dpp_u<CTRL>(k[REV ? 7 - r : r]);
-#pragma unroll
-  for (int r = 0; r < 8; ++r) k[r] = lower ? min(k[r], o[r]) : max(k[r], o[r]);
+template <int CTRL>
+__device__ inline float dpp_f(float v) {
+  return __uint_as_float(dpp_u<CTRL>(__float_as_uint(v)));
 }
-// half-cleaner inside a lane: registers r and r + J (r & J == 0) ordered ascending
-template <int J>
-__device__ inline void net_local(uint32_t (&k)[8]) {
-#pragma unroll
-  for (int r = 0; r < 8; ++r)
-    if (!(r & J)) {
-      const uint32_t lo = min(k[r], k[r + J]), hi = max(k[r], k[r + J]);
-      k[r] = lo;
-      k[r + J] = hi;
-    }
-}
-
-// Sort the 64 keys of an 8-lane group, element 8p + r on lane p, register r, when each
-// lane's eight registers already ascend: the three merge levels of a bitonic network
-// whose first step in each level pairs mirror images (so every run is merged ascending).
-__device__ inline void sort_group64(uint32_t (&k)[8], int p) {
-  // runs of 16: lanes p, p ^ 1
-  net_cross<kDppXor1, true>(k, (p & 1) == 0);
-  net_local<4>(k); net_local<2>(k); net_local<1>(k);
-  // runs of 32: lanes of a quad, mirrored, then p ^ 1
-  net_cross<kDppQuadMirror, true>(k, (p & 2) == 0);
-  net_cross<kDppXor1, false>(k, (p & 1) == 0);
-  net_local<4>(k); net_local<2>(k); net_local<1>(k);
-  // runs of 64: the 8 lanes mirrored, then p ^ 2, p ^ 1
-  net_cross<kDppHalfMirror, true>(k, (p & 4) == 0);
-  net_cross<kDppXor2, false>(k, (p & 2) == 0);
-  net_cross<kDppXor1, false>(k, (p & 1) == 0);
-  net_local<4>(k); net_local<2>(k); net_local<1>(k);
-}
-
 template <int CTRL>
 __device__ inline double dpp_d(double v) {
   const uint64_t u = (uint64_t)__double_as_longlong(v);
@@ -93,51 +60,77 @@ __device__ inline double dpp_d(double v) {
   return __longlong_as_double((long long)(lo | (hi << 32)));
 }
 
-// exclusive prefix over the 8 lanes of a group (lane p gets the sum of lanes < p)
-__device__ inline double group_excl8(double x, int p) {
-  double s = x, t;
-  t = dpp_d<kDppShr1>(s);
-  s += p >= 1 ? t : 0.0;
-  t = dpp_d<kDppShr2>(s);
-  s += p >= 2 ? t : 0.0;
-  t = dpp_d<kDppShr4>(s);
-  s += p >= 4 ? t : 0.0;
-  return s - x;
+// the smaller of a and b for z = 0, the larger for z = ~0 (one v_med3_u32)
+__device__ inline uint32_t pick(uint32_t a, uint32_t b, uint32_t z) { return max(min(a, b), min(max(a, b), z)); }
+
+// One cross-lane step of the sorting network: register r meets the partner lane's
+// register r (or 15 - r with REV); the lane with z = 0 keeps the smaller key.
+template <int CTRL, bool REV>
+__device__ inline void net_cross(uint32_t (&k)[16], uint32_t z) {
+  uint32_t o[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) o[r] = dpp_u<CTRL>(k[REV ? 15 - r : r]);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) k[r] = pick(k[r], o[r], z);
+}
+__device__ inline void order2(uint32_t& a, uint32_t& b) {
+  const uint32_t lo = min(a, b), hi = max(a, b);
+  a = lo;
+  b = hi;
+}
+// half-cleaner inside a lane
+template <int J>
+__device__ inline void net_half(uint32_t (&k)[16]) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r)
+    if (!(r & J)) order2(k[r], k[r + J]);
+}
+// a lane's bitonic sequence of 16 sorted ascending
+__device__ inline void net_local16(uint32_t (&k)[16]) {
+  net_half<8>(k); net_half<4>(k); net_half<2>(k); net_half<1>(k);
+}
+// step of the odd-even merge of registers 0-7 with registers 8-15
+template <int J>
+__device__ inline void net_odd_even(uint32_t (&k)[16]) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r)
+    if ((r & J) && r + J < 16) order2(k[r], k[r + J]);
 }
 
-// reduce-scatter over the 8 lanes of a group: lane p gets the sum over the lanes of
-// their d[p].  Three halving steps, each with a partner whose lane differs in the bit
-// that decides which half of the remaining entries a lane keeps.
-__device__ inline double group_reduce_scatter8(const double (&d)[8], int p) {
-  double h[4], q[2];
-  const bool k4 = p & 4, k2 = p & 2, k1 = p & 1;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {   // partner 7 - p: the other bit 2
-    const double keep = k4 ? d[i + 4] : d[i], send = k4 ? d[i] : d[i + 4];
-    h[i] = keep + dpp_d<kDppHalfMirror>(send);
-  }
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {   // partner p ^ 3: the same bit 2, the other bit 1
-    const double keep = k2 ? h[i + 2] : h[i], send = k2 ? h[i] : h[i + 2];
-    q[i] = keep + dpp_d<kDppQuadMirror>(send);
-  }
-  const double keep = k1 ? q[1] : q[0], send = k1 ? q[0] : q[1];
-  return keep + dpp_d<kDppXor1>(send);
+// Sort the 64 keys of a quad, element 16 q + r on lane q, register r, when registers
+// 0-7 and registers 8-15 of every lane already ascend.  z1 / z2: ~0 where bit 0 / bit 1
+// of q is set, else 0.
+__device__ inline void sort_quad64(uint32_t (&k)[16], uint32_t z1, uint32_t z2) {
+  // runs of 16: the lane's two rows (odd-even merge, 25 exchanges)
+  net_half<8>(k); net_odd_even<4>(k); net_odd_even<2>(k); net_odd_even<1>(k);
+  // runs of 32: lanes q, q ^ 1, mirrored
+  net_cross<kDppXor1, true>(k, z1);
+  net_local16(k);
+  // runs of 64: the quad mirrored, then q ^ 1
+  net_cross<kDppQuadMirror, true>(k, z2);
+  net_cross<kDppXor1, false>(k, z1);
+  net_local16(k);
 }
 
-// lane r of this lane's group of eight (ds_swizzle bit mode: and 0x18, or r)
-template <int R>
-__device__ inline float group_bcast(float v) {
-  return __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(v), 0x18 | (R << 5)));
+// orders this wave's LDS accesses (its other lanes' data): LDS serves a wave in order,
+// so only the compiler has to keep the order
+__device__ inline void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
+
+// LDS of one wave: per bin 68 doubles (neighbouring bins eight banks apart) that hold in
+// turn the 64 pair sums, the running weights, the running integrals and the sorted
+// values.  Sorted element 16 q + r sits in slot 4 r + q, so a quad's stores are
+// contiguous; slots 64-67 hold the running sums in front of each lane.
+constexpr int kCkSlots = 68;
 
 template <int S, bool CIA>
 __global__ __launch_bounds__(kBlock) void k_ck_mix(Model m, Work w, Tables tb, int B) {
-  // per wave: the 64 pair sums of each of its 8 bins, looked up after the sort; per
-  // block: the 64 pair weights w_a w_b (FP64)
-  __shared__ float s_val[kBlock / 64][512];
-  __shared__ double s_wpair[64];
-  if (threadIdx.x < 64) s_wpair[threadIdx.x] = tb.ckwd[threadIdx.x >> 3] * tb.ckwd[threadIdx.x & 7];
+  __shared__ double s_bin[kBlock / 64][kCkBinsPerWave * kCkSlots];
+  __shared__ double s_wpair[64];   // the 64 pair weights
+  if (threadIdx.x < 64) s_wpair[threadIdx.x] = ck_pair_weight(tb.ckwd[threadIdx.x >> 3], tb.ckwd[threadIdx.x & 7]);
   __syncthreads();
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -156,126 +149,150 @@ __global__ __launch_bounds__(kBlock) void k_ck_mix(Model m, Work w, Tables tb, i
   const __amdgpu_buffer_rsrc_t rh = make_rsrc(tb.h, (size_t)S * m.n_t * m.n_p * ncol * 4);
   const __amdgpu_buffer_rsrc_t rhc = make_rsrc(CIA ? (const void*)tb.hc : (const void*)tb.h,
                                                CIA ? (size_t)2 * m.n_tc * npad * 4 : 0);
-  // eight bins per pass, one per group of eight lanes; lane p of a group is g-point p
-  // of its bin and row p of each merge's pair matrix
-  const int grp = lane >> 3, p = lane & 7;
-  const double inv_wg = 1.0 / tb.ckwd[p];
-  float* vals = s_val[wv] + grp * 64;
-  float* out = w.ckmix + ((size_t)b * Lp + l) * ncol;
-
-  for (int t = 0; t < kCkBinsPerWave; t += 8) {
-    const int jr = j0 + t + grp;
-    const bool real = jr < m.n_nu;
-    const int j = real ? jr : m.n_nu - 1;   // a group past the last bin repeats it and stores nothing
-    const uint32_t col = (uint32_t)(j * kCkG + p);
-    // this lane's g-point of every absorber
-    float sp[S];
+  // lane q of quad grp: g-points 2q, 2q + 1 of bin j0 + grp
+  const int grp = lane >> 2, q = lane & 3;
+  const bool real = j0 + grp < m.n_nu;
+  const int j = real ? j0 + grp : m.n_nu - 1;   // a quad past the last bin repeats it and stores nothing
+  const uint32_t col = (uint32_t)(j * kCkG + 2 * q), voff = col * 4u;
+  float sp0[S], sp1[S];
 #pragma unroll
-    for (int s = 0; s < S; ++s) {
-      const uint32_t row = (uint32_t)((s * m.n_t + it) * m.n_p + ip) * row_bytes, voff = col * 4u;
-      float v = tb.c[(size_t)s * ncol + col] + rl[kRecFixed + s];
-      v = fmaf(w00, load_f32(rh, voff, row), v);
-      v = fmaf(w10, load_f32(rh, voff, row + tstep), v);
-      v = fmaf(w01, load_f32(rh, voff, row + row_bytes), v);
-      v = fmaf(w11, load_f32(rh, voff, row + tstep + row_bytes), v);
-      sp[s] = exp2_fast(v);
-    }
-    float mix = sp[0];   // the running mixture at g-point p: absorber 0 to start
-#pragma unroll
-    for (int s = 1; s < S; ++s) {
-      // row p of the pair matrix: mixture point p with each point r of absorber s, which
-      // ascends in r (a k-table row ascends in g)
-      float v[8];
-      v[0] = mix + group_bcast<0>(sp[s]);
-      v[1] = mix + group_bcast<1>(sp[s]);
-      v[2] = mix + group_bcast<2>(sp[s]);
-      v[3] = mix + group_bcast<3>(sp[s]);
-      v[4] = mix + group_bcast<4>(sp[s]);
-      v[5] = mix + group_bcast<5>(sp[s]);
-      v[6] = mix + group_bcast<6>(sp[s]);
-      v[7] = mix + group_bcast<7>(sp[s]);
-      // the previous merge's lookups are done before the table is rewritten
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      uint32_t key[8];
-#pragma unroll
-      for (int r = 0; r < 8; ++r) {
-        vals[8 * p + r] = v[r];
-        // optical depths are >= 0, so the bit patterns order like the values; the low
-        // six bits carry the pair index (pairs within 64 ulp may swap: < 4e-6 relative)
-        key[r] = (__float_as_uint(v[r]) & ~63u) | (uint32_t)(8 * p + r);
-      }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      sort_group64(key, p);
-      // The group's 64 pairs in sorted order, element 8p + r on lane p, and where each
-      // ends on the g axis, U_r.  The g bookkeeping runs in FP64: an interval edge often
-      // falls exactly on an element boundary (a negligible absorber leaves the pairs in
-      // blocks of one mixture point, whose weights sum to the edge), and there an FP32
-      // rounding of the running weight would move a sliver of the next, possibly far
-      // larger, value into the interval.
-      double vd[8], U[8];
-      double cs = 0.0;
-#pragma unroll
-      for (int r = 0; r < 8; ++r) {
-        const uint32_t idx = key[r] & 63u;
-        vd[r] = (double)vals[idx];
-        U[r] = s_wpair[idx];
-        cs += U[r];
-      }
-      const double c_lane = group_excl8(cs, p);
-      double run = c_lane;
-#pragma unroll
-      for (int r = 0; r < 8; ++r) {
-        run += U[r];
-        U[r] = run;
-      }
-      // D[n]: this lane's share of the integral of the sorted distribution over the
-      // g-interval [E_{n-1}, E_n], from the overlap of each element [U_{r-1}, U_r) with it
-      double D[8], prev = 0.0;
-#pragma unroll
-      for (int n = 0; n < kCkG; ++n) {
-        double part = 0.0;
-        if (n < kCkG - 1) {
-          const double E = tb.cke[n];
-          double lo = fmin(E, c_lane);
-#pragma unroll
-          for (int r = 0; r < 8; ++r) {
-            const double hi = fmin(E, U[r]);
-            part = fma(vd[r], hi - lo, part);
-            lo = hi;
-          }
-        } else {
-          double lo = c_lane;
-#pragma unroll
-          for (int r = 0; r < 8; ++r) {
-            part = fma(vd[r], U[r] - lo, part);
-            lo = U[r];
-          }
-        }
-        D[n] = part - prev;
-        prev = part;
-      }
-      // lane p: the integral over its own interval, summed over the group, / w_p
-      mix = (float)(group_reduce_scatter8(D, p) * inv_wg);
-    }
-    // grey continuum at the bin centre: deck, Rayleigh and the two CIA pairs
-    float dc = fmaf(ray, tb.nu4f[j], deck);
-    if (CIA) {
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        const uint32_t rowc = (uint32_t)(q * m.n_tc + itc) * (uint32_t)npad * 4u;
-        const uint32_t vo = (uint32_t)j * 4u;
-        float v = tb.cc[(size_t)q * npad + j] + rl[5 + q];
-        v = fmaf(1.0f - wtc, load_f32(rhc, vo, rowc), v);
-        v = fmaf(wtc, load_f32(rhc, vo, rowc + (uint32_t)npad * 4u), v);
-        dc += exp2_fast(v);
-      }
-    }
-    if (real) __builtin_nontemporal_store(mix + dc, &out[col]);   // read once, by the spectrum kernel
+  for (int s = 0; s < S; ++s) {
+    const uint32_t row = (uint32_t)((s * m.n_t + it) * m.n_p + ip) * row_bytes;
+    const float2 c = *reinterpret_cast<const float2*>(tb.c + (size_t)s * ncol + col);
+    const float lam = rl[kRecFixed + s];
+    const float2 t00 = load_f32x2(rh, voff, row), t10 = load_f32x2(rh, voff, row + tstep);
+    const float2 t01 = load_f32x2(rh, voff, row + row_bytes), t11 = load_f32x2(rh, voff, row + tstep + row_bytes);
+    float v0 = c.x + lam, v1 = c.y + lam;
+    v0 = fmaf(w00, t00.x, v0);
+    v1 = fmaf(w00, t00.y, v1);
+    v0 = fmaf(w10, t10.x, v0);
+    v1 = fmaf(w10, t10.y, v1);
+    v0 = fmaf(w01, t01.x, v0);
+    v1 = fmaf(w01, t01.y, v1);
+    v0 = fmaf(w11, t11.x, v0);
+    v1 = fmaf(w11, t11.y, v1);
+    sp0[s] = exp2_fast(v0);
+    sp1[s] = exp2_fast(v1);
   }
+  const uint32_t z1 = (q & 1) ? ~0u : 0u, z2 = (q & 2) ? ~0u : 0u;
+  const double g1 = q > 0 ? 1.0 : 0.0, g2 = q > 1 ? 1.0 : 0.0, g3 = q > 2 ? 1.0 : 0.0;
+  const double e0 = tb.cke[2 * q], e1 = tb.cke[2 * q + 1];
+  const double inv0 = 1.0 / tb.ckwd[2 * q], inv1 = 1.0 / tb.ckwd[2 * q + 1];
+  double* sums = s_bin[wv] + grp * kCkSlots;
+  float* vals = reinterpret_cast<float*>(sums);
+  auto sum_at = [&](uint32_t byte) { return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(sums) + byte); };
+  // sum over the quad's lanes below this one
+  auto quad_excl = [&](double t) {
+    return fma(dpp_d<dpp_quad_lane(0)>(t), g1, fma(dpp_d<dpp_quad_lane(1)>(t), g2, dpp_d<dpp_quad_lane(2)>(t) * g3));
+  };
+
+  float mix0 = sp0[0], mix1 = sp1[0];   // the running mixture: absorber 0 to start
+#pragma unroll
+  for (int s = 1; s < S; ++s) {
+    // rows 2q and 2q + 1 of the pair matrix
+    float v[16];
+    {
+      const float b0 = dpp_f<dpp_quad_lane(0)>(sp0[s]), b1 = dpp_f<dpp_quad_lane(0)>(sp1[s]);
+      const float b2 = dpp_f<dpp_quad_lane(1)>(sp0[s]), b3 = dpp_f<dpp_quad_lane(1)>(sp1[s]);
+      const float b4 = dpp_f<dpp_quad_lane(2)>(sp0[s]), b5 = dpp_f<dpp_quad_lane(2)>(sp1[s]);
+      const float b6 = dpp_f<dpp_quad_lane(3)>(sp0[s]), b7 = dpp_f<dpp_quad_lane(3)>(sp1[s]);
+      const float br[8] = {b0, b1, b2, b3, b4, b5, b6, b7};
+#pragma unroll
+      for (int r = 0; r < 8; ++r) {
+        v[r] = mix0 + br[r];
+        v[8 + r] = mix1 + br[r];
+      }
+    }
+    wave_lds_fence();   // the previous merge's lookups are done before the tables are rewritten
+    uint32_t key[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      vals[16 * q + r] = v[r];
+      // optical depths are >= 0, so the bit patterns order like the values; the low
+      // six bits carry the pair index (pairs within 64 ulp may swap: < 4e-6 relative)
+      key[r] = (__float_as_uint(v[r]) & ~63u) | (uint32_t)(16 * q + r);
+    }
+    wave_lds_fence();
+    sort_quad64(key, z1, z2);
+    // The running weight U in front of each sorted element (from the lane's first one),
+    // in FP64: an interval edge often falls exactly on an element boundary (a negligible
+    // absorber leaves the pairs in blocks of one mixture point, whose weights sum to the
+    // edge), and there a rounding of the running weight would move a sliver of the next,
+    // possibly far larger, value into the interval.  The pair weights are whole multiples
+    // of 2^-52 and so are the edges, so every such sum and difference is exact.
+    float vs[16];
+    double ie[16], i_lane;   // the integral in front of each element, from the lane's first one
+    {
+      double wr[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const uint32_t idx = key[r] & 63u;
+        vs[r] = vals[idx];
+        wr[r] = s_wpair[idx];
+      }
+      wave_lds_fence();
+      double u = 0.0, isum = 0.0;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        sums[4 * r + q] = u;
+        ie[r] = isum;
+        u += wr[r];
+        isum = fma((double)vs[r], wr[r], isum);
+      }
+      sums[64 + q] = quad_excl(u);
+      i_lane = quad_excl(isum);
+    }
+    wave_lds_fence();
+    // the element holding each edge, the last one whose U is at most the edge (U_0 = 0):
+    // its lane, then its register (slots 4 r + lane)
+    const uint32_t h0 = sum_at(512 + 16) <= e0 ? 16u : 0u, h1 = sum_at(512 + 16) <= e1 ? 16u : 0u;
+    uint32_t a0 = h0 + (sum_at(512 + 8 + h0) <= e0 ? 8u : 0u), a1 = h1 + (sum_at(512 + 8 + h1) <= e1 ? 8u : 0u);
+    const uint32_t l0 = 512 + a0, l1 = 512 + a1;
+    double x0 = e0 - sum_at(l0), x1 = e1 - sum_at(l1);
+    auto probe = [&](uint32_t step) {
+      const double u0 = sum_at(a0 + step), u1 = sum_at(a1 + step);
+      a0 += u0 <= x0 ? step : 0u;
+      a1 += u1 <= x1 ? step : 0u;
+    };
+    probe(256);
+    probe(128);
+    probe(64);
+    probe(32);
+    x0 -= sum_at(a0);
+    x1 -= sum_at(a1);
+    wave_lds_fence();
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sums[4 * r + q] = ie[r];
+    sums[64 + q] = i_lane;
+    wave_lds_fence();
+    double f0 = sum_at(l0) + sum_at(a0), f1 = sum_at(l1) + sum_at(a1);
+    wave_lds_fence();
+#pragma unroll
+    for (int r = 0; r < 16; ++r) vals[4 * r + q] = vs[r];
+    wave_lds_fence();
+    f0 = fma((double)vals[a0 >> 3], x0, f0);
+    f1 = fma((double)vals[a1 >> 3], x1, f1);
+    // interval 2q starts at the previous lane's second edge
+    const double fp = dpp_d<kDppQuadPrev>(f1);
+    mix0 = (float)((f0 - (q > 0 ? fp : 0.0)) * inv0);
+    mix1 = (float)((f1 - f0) * inv1);
+  }
+  // grey continuum at the bin centre: deck, Rayleigh and the two CIA pairs
+  float dc = fmaf(ray, tb.nu4f[j], deck);
+  if (CIA) {
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const uint32_t rowc = (uint32_t)(p * m.n_tc + itc) * (uint32_t)npad * 4u;
+      const uint32_t vo = (uint32_t)j * 4u;
+      float v = tb.cc[(size_t)p * npad + j] + rl[5 + p];
+      v = fmaf(1.0f - wtc, load_f32(rhc, vo, rowc), v);
+      v = fmaf(wtc, load_f32(rhc, vo, rowc + (uint32_t)npad * 4u), v);
+      dc += exp2_fast(v);
+    }
+  }
+  if (real)   // read once, by the spectrum kernel
+    __builtin_nontemporal_store((float2v){mix0 + dc, mix1 + dc},
+                                reinterpret_cast<float2v*>(w.ckmix + ((size_t)b * Lp + l) * ncol + col));
 }
 
 // Transmission: per (sample, 128-column tile) the chord tau = P dtau on MFMA
@@ -392,12 +409,6 @@ __global__ __launch_bounds__(kBlockT) void k_ck_trans(Model m, Work w, Tables tb
 // (bin, row).  One absorber per pass keeps a wave's table loads on 16 contiguous
 // bins of one table row.
 constexpr int kProdBins = kTileNu / kCkG;   // bins per tile
-
-// two adjacent FP32 table entries (8 bytes) through a buffer resource
-__device__ inline float2 load_f32x2(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-  const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0);
-  return make_float2(__uint_as_float(v[0]), __uint_as_float(v[1]));
-}
 
 template <int S, bool CIA>
 __global__ __launch_bounds__(kBlockT) void k_ck_trans_prod(Model m, Work w, Tables tb, int B,

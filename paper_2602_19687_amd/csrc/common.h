@@ -34,7 +34,7 @@ constexpr int kBlock = 256;       // threads per workgroup (4 wave64)
 constexpr int kBlockT = 512;      // threads per workgroup of the reduced-precision transmission kernels
 constexpr int kShortLayers = 128;  // layer capacity of the short class of a ragged reduced-precision batch
 constexpr int kCkG = 8;           // g-points per bin of a correlated-k table
-constexpr int kCkBinsPerWave = 16;  // bins one wave of the k-distribution mixing kernel walks through
+constexpr int kCkBinsPerWave = 16;  // bins of one wave of the k-distribution mixing kernel, a quad of lanes each
 // a chord optical depth beyond which e^-tau is zero in FP32 with a wide margin
 // (e^-103.3 is already below the smallest denormal): its adjoint seed is exactly 0
 constexpr float kOpaqueTau = 110.0f;
@@ -47,6 +47,12 @@ constexpr float kOpaqueTau = 110.0f;
 // q_l rho_l dr_l 3 / (4 r_eff) that multiplies Q_ext(nu).
 constexpr int kRecFixed = 7;
 __host__ __device__ constexpr int rec_len(int s) { return kRecFixed + s; }
+
+// Weight of a pair of g-points in the k-distribution mixing, as a whole multiple of 2^-52:
+// running sums of such weights (at most 1) are exact in FP64 in any order
+__host__ __device__ inline double ck_pair_weight(double wa, double wb) {
+  return rint(wa * wb * 4503599627370496.0) * 2.220446049250313080847e-16;
+}
 
 // packed interpolation cells of one layer: iT | iP << 8 | iTc << 16
 __host__ __device__ inline int pack_cells(int it, int ip, int itc) { return it | (ip << 8) | (itc << 16); }
@@ -148,7 +154,7 @@ struct Tables {
   const double* nu4d;    // fp64: [n_nu_pad]
   const float* ckw;      // correlated-k: [kCkG] g-point weights
   const double* ckwd;    // correlated-k: [kCkG] g-point weights in FP64 (the mixing's bookkeeping)
-  const double* cke;     // correlated-k: [kCkG] upper edges of the g-intervals (running sums of the weights)
+  const double* cke;     // correlated-k: [kCkG] upper edges of the g-intervals (running sums of the pair weights)
 };
 
 }  // namespace exofwd

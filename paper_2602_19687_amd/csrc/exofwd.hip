@@ -520,7 +520,7 @@ exofwd_status exofwd_create(const exofwd_config* cfg, exofwd_ctx** out) {
       for (int i = 0; i < kCkG; ++i) {
         wv[i] = (float)g.ck_weights[i];
         wd[i] = g.ck_weights[i];
-        run += g.ck_weights[i];
+        for (int k2 = 0; k2 < kCkG; ++k2) run += ck_pair_weight(g.ck_weights[i], g.ck_weights[k2]);
         ev[i] = run;
       }
       float* dw = A(dalloc<float>(c, kCkG));
