@@ -19,8 +19,8 @@
 //   because both distributions do.  The 64 pair sums are sorted by three merge levels:
 //   the lane's two rows (an odd-even merge of registers), then two lanes, then the quad
 //   (bitonic, quad_perm moves between lanes); keys = the value's bits above the low
-//   six, the pair index in the low six.  The exact sums and weights are looked up by
-//   index, their running sums (weights U, weights x values I, FP64) go to LDS in sorted
+//   six, a code of the pair in the low six.  The exact sums and weights are looked up by
+//   code, their running sums (weights U, weights x values I, FP64) go to LDS in sorted
 //   order, and each lane finds its two g-interval edges there by bisection: the integral
 //   of the sorted distribution up to an edge E inside element r is I_r + v_r (E - U_r).
 //   Output: the mixed layer optical depths [B][L_pad][n_bins_pad x 8] (FP32), read by
@@ -120,17 +120,33 @@ __device__ inline void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// LDS of one wave: per bin 68 doubles (neighbouring bins eight banks apart) that hold in
-// turn the 64 pair sums, the running weights, the running integrals and the sorted
-// values.  Sorted element 16 q + r sits in slot 4 r + q, so a quad's stores are
-// contiguous; slots 64-67 hold the running sums in front of each lane.
+// Bound by the vector unit and the LDS together (88 % and 84 % of their cycles busy at
+// 256 samples x 100 layers x 2485 bins x 8 absorbers, 29.4 ms; eight lanes per bin with
+// every element's overlap with every interval took 50.8 ms: 670 vector instructions per
+// merge of eight bins, now 270).  Four waves per SIMD: 116 registers, 36 KB per block.
+//
+// LDS of one wave, used in turn for the pair sums, the running weights, the running
+// integrals and the sorted values of its 16 bins.  The kernel keeps the LDS as busy as
+// the vector unit, so each layout keeps a lane off its neighbours' banks:
+//   pair sums: the pair of code c of bin g at float 8 c + g % 8 (+ 512 for the upper
+//     eight bins), so a bin's lookups, at four random codes at a time, stay in its own
+//     eight banks; the code of register r on lane q is r ^ 18 q (row c / 8, and the
+//     column xor 2 q), so the four lanes of a quad store to different banks;
+//   running sums: slot n of bin g at double kCkInter n + g % kCkInter (the bins in groups
+//     of kCkInter); sorted element 16 q + r in slot 4 r + q, so the stores fill the
+//     banks; slots 64-67 hold the sums in front of each lane.
+// The pair weights are kept in kCkInter copies, bin g reading copy g % kCkInter.
 constexpr int kCkSlots = 68;
+constexpr int kCkInter = 4;
 
 template <int S, bool CIA>
 __global__ __launch_bounds__(kBlock) void k_ck_mix(Model m, Work w, Tables tb, int B) {
   __shared__ double s_bin[kBlock / 64][kCkBinsPerWave * kCkSlots];
-  __shared__ double s_wpair[64];   // the 64 pair weights
-  if (threadIdx.x < 64) s_wpair[threadIdx.x] = ck_pair_weight(tb.ckwd[threadIdx.x >> 3], tb.ckwd[threadIdx.x & 7]);
+  __shared__ double s_wpair[64 * kCkInter];   // the pair weights by code
+  for (int i = threadIdx.x; i < 64 * kCkInter; i += kBlock) {
+    const int c = i / kCkInter, row = c >> 3;
+    s_wpair[i] = ck_pair_weight(tb.ckwd[row], tb.ckwd[(c & 7) ^ (row & 6)]);
+  }
   __syncthreads();
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -178,9 +194,17 @@ __global__ __launch_bounds__(kBlock) void k_ck_mix(Model m, Work w, Tables tb, i
   const double g1 = q > 0 ? 1.0 : 0.0, g2 = q > 1 ? 1.0 : 0.0, g3 = q > 2 ? 1.0 : 0.0;
   const double e0 = tb.cke[2 * q], e1 = tb.cke[2 * q + 1];
   const double inv0 = 1.0 / tb.ckwd[2 * q], inv1 = 1.0 / tb.ckwd[2 * q + 1];
-  double* sums = s_bin[wv] + grp * kCkSlots;
-  float* vals = reinterpret_cast<float*>(sums);
+  float* pairs = reinterpret_cast<float*>(s_bin[wv]) + (grp & 7) + 512 * (grp >> 3);
+  double* sums = s_bin[wv] + (grp % kCkInter) + kCkInter * kCkSlots * (grp / kCkInter);
+  float* vals = reinterpret_cast<float*>(sums);   // the sorted values, in the low half of each slot
+  const double* wpair = s_wpair + (grp & (kCkInter - 1));
+  constexpr uint32_t kSlotB = 8 * kCkInter, kLaneB = kSlotB, kRegB = 4 * kSlotB, kTopB = 64 * kSlotB;
   auto sum_at = [&](uint32_t byte) { return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(sums) + byte); };
+  auto val_at = [&](uint32_t byte) { return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(vals) + byte); };
+  // codes of the registers: pair_code[j] + 8 i + k for register 8 i + 2 j + k
+  uint32_t pair_code[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) pair_code[k] = (uint32_t)(16 * q + 2 * (k ^ q));
   // sum over the quad's lanes below this one
   auto quad_excl = [&](double t) {
     return fma(dpp_d<dpp_quad_lane(0)>(t), g1, fma(dpp_d<dpp_quad_lane(1)>(t), g2, dpp_d<dpp_quad_lane(2)>(t) * g3));
@@ -207,10 +231,11 @@ __global__ __launch_bounds__(kBlock) void k_ck_mix(Model m, Work w, Tables tb, i
     uint32_t key[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      vals[16 * q + r] = v[r];
+      const uint32_t c0 = pair_code[(r >> 1) & 3], ik = (uint32_t)((r & 8) | (r & 1));
+      pairs[8 * c0 + 8 * ik] = v[r];
       // optical depths are >= 0, so the bit patterns order like the values; the low
-      // six bits carry the pair index (pairs within 64 ulp may swap: < 4e-6 relative)
-      key[r] = (__float_as_uint(v[r]) & ~63u) | (uint32_t)(16 * q + r);
+      // six bits carry the pair's code (pairs within 64 ulp may swap: < 4e-6 relative)
+      key[r] = ((__float_as_uint(v[r]) & ~63u) | c0) | ik;
     }
     wave_lds_fence();
     sort_quad64(key, z1, z2);
@@ -226,52 +251,54 @@ __global__ __launch_bounds__(kBlock) void k_ck_mix(Model m, Work w, Tables tb, i
       double wr[16];
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const uint32_t idx = key[r] & 63u;
-        vs[r] = vals[idx];
-        wr[r] = s_wpair[idx];
+        const uint32_t code = key[r] & 63u;
+        vs[r] = pairs[8 * code];
+        wr[r] = wpair[kCkInter * code];
       }
       wave_lds_fence();
       double u = 0.0, isum = 0.0;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        sums[4 * r + q] = u;
+        sums[kCkInter * (4 * r + q)] = u;
         ie[r] = isum;
         u += wr[r];
         isum = fma((double)vs[r], wr[r], isum);
       }
-      sums[64 + q] = quad_excl(u);
+      sums[kCkInter * (64 + q)] = quad_excl(u);
       i_lane = quad_excl(isum);
     }
     wave_lds_fence();
     // the element holding each edge, the last one whose U is at most the edge (U_0 = 0):
     // its lane, then its register (slots 4 r + lane)
-    const uint32_t h0 = sum_at(512 + 16) <= e0 ? 16u : 0u, h1 = sum_at(512 + 16) <= e1 ? 16u : 0u;
-    uint32_t a0 = h0 + (sum_at(512 + 8 + h0) <= e0 ? 8u : 0u), a1 = h1 + (sum_at(512 + 8 + h1) <= e1 ? 8u : 0u);
-    const uint32_t l0 = 512 + a0, l1 = 512 + a1;
+    const uint32_t h0 = sum_at(kTopB + 2 * kLaneB) <= e0 ? 2 * kLaneB : 0u;
+    const uint32_t h1 = sum_at(kTopB + 2 * kLaneB) <= e1 ? 2 * kLaneB : 0u;
+    uint32_t a0 = h0 + (sum_at(kTopB + kLaneB + h0) <= e0 ? kLaneB : 0u);
+    uint32_t a1 = h1 + (sum_at(kTopB + kLaneB + h1) <= e1 ? kLaneB : 0u);
+    const uint32_t l0 = kTopB + a0, l1 = kTopB + a1;
     double x0 = e0 - sum_at(l0), x1 = e1 - sum_at(l1);
     auto probe = [&](uint32_t step) {
       const double u0 = sum_at(a0 + step), u1 = sum_at(a1 + step);
       a0 += u0 <= x0 ? step : 0u;
       a1 += u1 <= x1 ? step : 0u;
     };
-    probe(256);
-    probe(128);
-    probe(64);
-    probe(32);
+    probe(8 * kRegB);
+    probe(4 * kRegB);
+    probe(2 * kRegB);
+    probe(kRegB);
     x0 -= sum_at(a0);
     x1 -= sum_at(a1);
     wave_lds_fence();
 #pragma unroll
-    for (int r = 0; r < 16; ++r) sums[4 * r + q] = ie[r];
-    sums[64 + q] = i_lane;
+    for (int r = 0; r < 16; ++r) sums[kCkInter * (4 * r + q)] = ie[r];
+    sums[kCkInter * (64 + q)] = i_lane;
     wave_lds_fence();
     double f0 = sum_at(l0) + sum_at(a0), f1 = sum_at(l1) + sum_at(a1);
     wave_lds_fence();
 #pragma unroll
-    for (int r = 0; r < 16; ++r) vals[4 * r + q] = vs[r];
+    for (int r = 0; r < 16; ++r) vals[2 * kCkInter * (4 * r + q)] = vs[r];
     wave_lds_fence();
-    f0 = fma((double)vals[a0 >> 3], x0, f0);
-    f1 = fma((double)vals[a1 >> 3], x1, f1);
+    f0 = fma((double)val_at(a0), x0, f0);
+    f1 = fma((double)val_at(a1), x1, f1);
     // interval 2q starts at the previous lane's second edge
     const double fp = dpp_d<kDppQuadPrev>(f1);
     mix0 = (float)((f0 - (q > 0 ? fp : 0.0)) * inv0);
