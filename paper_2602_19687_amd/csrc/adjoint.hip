@@ -22,8 +22,6 @@
 
 namespace exofwd {
 
-typedef __attribute__((ext_vector_type(4))) double f64x4;
-
 // a float pair read once (stored dtau_bar): a non-temporal load
 __device__ inline float2 ld_stream2(const float* p) {
   const float2v v = __builtin_nontemporal_load(reinterpret_cast<const float2v*>(p));

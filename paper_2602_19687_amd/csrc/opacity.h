@@ -274,4 +274,132 @@ __device__ inline void frag_hl(const uint32_t* x, bf16x8& hi, bf16x8& lo) {
   lo = __builtin_bit_cast(bf16x8, make_uint4(l[0], l[1], l[2], l[3]));
 }
 
+// ---------------------------------------------------------------------------
+// Plain FP64 form: log10 sigma tables read as they are, one wavenumber per lane.
+
+// 2^x for finite x (0 or infinity past the exponent range): the fractional part, in
+// [-1/2, 1/2], through a degree-11 polynomial (1 + f q(f), q interpolating (2^f - 1)/f
+// at the Chebyshev points of the interval; 2e-17 relative)
+__device__ inline double exp2_d(double x) {
+  const double n = __builtin_rint(x), f = x - n;
+  double q = 4.4549605981865186e-10;
+  q = fma(q, f, 7.072585949269223e-09);
+  q = fma(q, f, 1.0178062445845774e-07);
+  q = fma(q, f, 1.321544258792169e-06);
+  q = fma(q, f, 1.525273382983612e-05);
+  q = fma(q, f, 0.0001540353044173605);
+  q = fma(q, f, 0.0013333558146416936);
+  q = fma(q, f, 0.009618129107606888);
+  q = fma(q, f, 0.0555041086648216);
+  q = fma(q, f, 0.24022650695910097);
+  q = fma(q, f, 0.6931471805599453);
+  return __builtin_ldexp(fma(q, f, 1.0), (int)n);
+}
+// e^-tau for tau >= 0 (infinite included; a NaN stays one)
+__device__ inline double exp_neg_d(double tau) {
+  const double x = -1.4426950408889634074 * tau;
+  return exp2_d(x < -1100.0 ? -1100.0 : x);
+}
+
+// Table entries of one layer at this lane's wavenumber: four bilinear corners (T and log p
+// steps: 00, 10, 01, 11) per line source, two T rows per CIA pair.
+template <int S, bool CIA>
+struct LayerRows64 {
+  double t[4 * S + (CIA ? 4 : 0)];
+};
+
+template <int S, bool CIA>
+__device__ inline void fetch_rows64(const Model& m, const Tables& tb, int cl, int nu, LayerRows64<S, CIA>& r) {
+  const int it = cl & 255, ip = (cl >> 8) & 255, itc = cl >> 16;
+  const size_t npad = (size_t)m.n_nu_pad, tstep = (size_t)m.n_p * npad;
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    const double* p = tb.t64 + (((size_t)s * m.n_t + it) * m.n_p + ip) * npad;
+    r.t[4 * s] = p[nu];
+    r.t[4 * s + 1] = (p + tstep)[nu];
+    r.t[4 * s + 2] = (p + npad)[nu];
+    r.t[4 * s + 3] = (p + tstep + npad)[nu];
+  }
+  if constexpr (CIA) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const double* p = tb.tc64 + ((size_t)c * m.n_tc + itc) * npad;
+      r.t[4 * S + 2 * c] = p[nu];
+      r.t[4 * S + 2 * c + 1] = (p + npad)[nu];
+    }
+  }
+}
+
+// Optical depth of one layer (record rl) from its table entries; qext multiplies the cloud
+// column (1 for the grey deck).  The bilinear weights carry the factor log2(10).
+template <int S, bool CIA>
+__device__ inline double eval_rows64(const double* __restrict__ rl, const LayerRows64<S, CIA>& r, double nu4,
+                                     double qext) {
+  const double wt = rl[0], wp = rl[1];
+  const double a = (1.0 - wp) * kLog2_10, b = wp * kLog2_10;
+  const double w00 = (1.0 - wt) * a, w10 = wt * a, w01 = (1.0 - wt) * b, w11 = wt * b;
+  double acc = fma(rl[3], nu4, rl[4] * qext);
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    double x = fma(w00, r.t[4 * s], rl[kRecFixed + s]);
+    x = fma(w10, r.t[4 * s + 1], x);
+    x = fma(w01, r.t[4 * s + 2], x);
+    acc += exp2_d(fma(w11, r.t[4 * s + 3], x));
+  }
+  if constexpr (CIA) {
+    const double wc = rl[2] * kLog2_10, wc0 = (1.0 - rl[2]) * kLog2_10;
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+      acc += exp2_d(fma(wc, r.t[4 * S + 2 * c + 1], fma(wc0, r.t[4 * S + 2 * c], rl[5 + c])));
+  }
+  return acc;
+}
+
+// Line and CIA terms t of one layer with the derivative dw of each exponent with respect
+// to its T weight (log2 units), formed from the differences of the table entries.
+template <int S, bool CIA>
+__device__ inline void eval_rows64_deriv(const double* __restrict__ rl, const LayerRows64<S, CIA>& r, double* t,
+                                         double* dw) {
+  const double wt = rl[0], a = (1.0 - rl[1]) * kLog2_10, b = rl[1] * kLog2_10;
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    const double t00 = r.t[4 * s], t10 = r.t[4 * s + 1], t01 = r.t[4 * s + 2], t11 = r.t[4 * s + 3];
+    dw[s] = fma(b, t11 - t01, a * (t10 - t00));
+    t[s] = exp2_d(fma(wt, dw[s], fma(b, t01, fma(a, t00, rl[kRecFixed + s]))));
+  }
+  if constexpr (CIA) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const double t0 = r.t[4 * S + 2 * c], t1 = r.t[4 * S + 2 * c + 1];
+      dw[S + c] = (t1 - t0) * kLog2_10;
+      t[S + c] = exp2_d(fma(rl[2], dw[S + c], fma(kLog2_10, t0, rl[5 + c])));
+    }
+  }
+}
+
+// ---- FP64 chord products on v_mfma_f64_16x16x4f64 (a matrix product of the same rate as
+// the vector FMAs, issued beside them): 16 x 16 tiles, k in blocks of 16 split over the
+// lane quarters h = lane / 16 as k = 16 K + 4 h + step, so a lane's four entries of a row
+// are contiguous.  A: row lane % 16; B: column lane % 16; D: row h + 4 e in element e.
+typedef __attribute__((ext_vector_type(4))) double f64x4;
+
+constexpr int kMaxBlocks16 = kMaxLayers / 16;
+// layers rounded up to a whole 16-row block: the rows of the FP64 kernels' LDS tiles
+__host__ __device__ constexpr int rows16(int layers) { return (layers + 15) / 16 * 16; }
+
+// 16-row blocks of `part` of `parts` (2 or 4): each block in turn, the costliest first,
+// goes to the part with the least cost so far; block i of nb costs nb - i, or i + 1 with `rev`
+__device__ inline unsigned split_blocks16(int part, int parts, int nb, bool rev) {
+  unsigned mine = 0;
+  int c[4] = {0, 0, 0, 0};
+  for (int q = 0; q < nb; ++q) {
+    int best = 0;
+    for (int p = 1; p < parts; ++p)
+      if (c[p] < c[best]) best = p;
+    if (best == part) mine |= 1u << (rev ? nb - 1 - q : q);
+    c[best] += nb - q;
+  }
+  return mine;
+}
+
 }  // namespace exofwd
