@@ -20,6 +20,8 @@
 #include "opacity.h"
 #include "tp.h"
 
+#include <climits>
+
 namespace exofwd {
 
 // a float pair read once (stored dtau_bar): a non-temporal load
@@ -647,222 +649,333 @@ __global__ __launch_bounds__(kBlock) void k_cloud_spectral(Model m, Work w, AdjW
 }
 
 // ============================================================================
-// FP64 reverse kernel: 512 threads, 64-wavenumber tiles, VALU chord products,
-// FP64 MFMA (16x16x4) for Pbar
-template <int S, bool CIA>
-__device__ inline void opacity_fp64_terms(const Model& m, const Tables& tb, int cl, const double* __restrict__ rl,
-                                          int nu, double nu4, double& dtau, double* t, double* dw, double qext = 1.0) {
-  const int it = cl & 255, ip = (cl >> 8) & 255, itc = cl >> 16;
-  const double wt = rl[0], wp = rl[1];
-  const size_t npad = (size_t)m.n_nu_pad;
-  double acc = rl[3] * nu4 + rl[4] * qext;   // the non-grey cloud's column times Q_ext(nu)
-#pragma unroll
-  for (int s = 0; s < S; ++s) {
-    const double* p = tb.t64 + (((size_t)s * m.n_t + it) * m.n_p + ip) * npad + nu;
-    const double t00 = p[0], t10 = p[(size_t)m.n_p * npad], t01 = p[npad], t11 = p[(size_t)(m.n_p + 1) * npad];
-    const double v = (1.0 - wt) * (1.0 - wp) * t00 + wt * (1.0 - wp) * t10 + (1.0 - wt) * wp * t01 + wt * wp * t11;
-    const double e = exp2(v * kLog2_10 + rl[kRecFixed + s]);
-    acc += e;
-    if (t) {
-      t[s] = e;
-      dw[s] = ((1.0 - wp) * (t10 - t00) + wp * (t11 - t01)) * kLog2_10;   // log2 units
-    }
-  }
-  if (CIA) {
-    const double wtc = rl[2];
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      const double* p = tb.tc64 + ((size_t)c * m.n_tc + itc) * npad + nu;
-      const double e = exp2(((1.0 - wtc) * p[0] + wtc * p[npad]) * kLog2_10 + rl[5 + c]);
-      acc += e;
-      if (t) {
-        t[S + c] = e;
-        dw[S + c] = (p[npad] - p[0]) * kLog2_10;
-      }
-    }
-  }
-  dtau = acc;
+// FP64 reverse kernel: 512 threads, one sample and wavenumber chunk per workgroup, every
+// product on v_mfma_f64_16x16x4f64
+
+template <int CTRL>
+__device__ inline double dpp_move(double v) {
+  const uint64_t u = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)u, CTRL, 0xF, 0xF, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), CTRL, 0xF, 0xF, true);
+  return __longlong_as_double((long long)((uint64_t)lo | ((uint64_t)hi << 32)));
 }
 
-// Two instances: TILE = 64 wavenumbers with ROWS = 16 rows per wave (L_pad <= 128),
-// and TILE = 32 with ROWS = 20 (L_pad <= 160: the tile's dtau and tau_bar, 2 TILE
-// (L_pad + 1) doubles, then fit in LDS; lanes 32-63 hold no wavenumber and add zeros).
-// PSLOTS: 16x16 Pbar tiles per wave.
-template <int S, bool CIA, int TILE, int ROWS, int PSLOTS>
+// a + b after the halves (ROW16: the odd 16-lane rows) of a and the other halves of b
+// changed places: lanes of the lower half get their a plus the upper half's a, lanes of
+// the upper half both halves' b
+template <bool ROW16>
+__device__ inline double swap_add(double a, double b) {
+  const uint64_t ua = (uint64_t)__double_as_longlong(a), ub = (uint64_t)__double_as_longlong(b);
+  auto sw = [](uint32_t x, uint32_t y) {
+    if constexpr (ROW16) return __builtin_amdgcn_permlane16_swap(x, y, false, false);
+    else return __builtin_amdgcn_permlane32_swap(x, y, false, false);
+  };
+  const auto lo = sw((uint32_t)ua, (uint32_t)ub), hi = sw((uint32_t)(ua >> 32), (uint32_t)(ub >> 32));
+  return __longlong_as_double((long long)((uint64_t)lo[0] | ((uint64_t)hi[0] << 32))) +
+         __longlong_as_double((long long)((uint64_t)lo[1] | ((uint64_t)hi[1] << 32)));
+}
+
+// Sums over the wave of 16 values per lane at once: the lanes of quad n (n = lane / 4) get
+// the sum of v[n].  Halving exchanges, about 60 instructions where a butterfly for each
+// value would take 18 each.
+__device__ inline double wave_sums16(double (&v)[16], int lane) {
+  double a[8], b[4], c[2];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) a[i] = swap_add<false>(v[i], v[i + 8]);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) b[i] = swap_add<true>(a[i], a[i + 4]);
+  const bool k8 = lane & 8, k4 = lane & 4;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {   // row_ror:8, the other eight lanes of the row
+    const double keep = k8 ? b[i + 2] : b[i], send = k8 ? b[i] : b[i + 2];
+    c[i] = keep + dpp_move<0x128>(send);
+  }
+  const double keep = k4 ? c[1] : c[0], send = k4 ? c[0] : c[1];
+  double r = keep + dpp_move<0x141>(send);   // row_half_mirror: the other quad of the eight
+  r += dpp_move<0xB1>(r);                    // quad_perm [1,0,3,2], then [2,3,0,1]
+  r += dpp_move<0x4E>(r);
+  return r;
+}
+
+// Per tile: the layer optical depths (each wave a contiguous run of layers) -> LDS; the
+// chords, seeds and tau_bar -> LDS; the path-matrix adjoint (accumulated in registers over
+// the chunk's tiles) and dtau_bar, which replaces the optical depths in LDS; the per-layer
+// sums, the layers above the tile's opaque frontier split evenly over the waves.  The
+// terms of the sums are formed again from the tables: recomputing costs less than the
+// registers or the memory traffic of keeping them.  A tile's tau_bar is zero (as exact
+// zeros) in the 16-row blocks below the frontier, whose products and sums are skipped.
+// Samples run fastest over the workgroups, so an XCD's workgroups read the same table
+// columns.  24 samples x 30000 wavenumbers x 100 layers x 6 absorbers: the whole FP64
+// gradient call 14.0 -> 4.2 ms (vector products with one LDS and one memory read per FMA,
+// 14 wave butterflies per layer and tile, and table columns no neighbour shared).
+//
+// TILE = 64 wavenumbers up to 128 padded layers; 32 (lanes 32-63 hold no wavenumber and add
+// zeros) up to 160, where two 64-wavenumber arrays no longer fit in LDS.
+template <int S, bool CIA, int TILE>
 __global__ __launch_bounds__(kBlockT) void k_trans_adj_fp64(Model m, Work w, Tables tb, AdjWork aw, int B, int C) {
+  constexpr int kWaves = kBlockT / 64, kNb = TILE / 16, kParts = kWaves / kNb, ld = TILE + 2;
+  constexpr int kMB = TILE == 64 ? 8 : 10;         // most 16-row blocks
+  constexpr int kSlots = TILE == 64 ? 4 : 3;       // row blocks of a wave (split_blocks16 of up to kMB blocks)
+  constexpr int kPSlots = (kMB * (kMB + 1) / 2 + kWaves - 1) / kWaves;   // 16x16 Pbar tiles of a wave
+  constexpr int NS = n_sums(S);
+  static_assert(NS <= 16, "wave_sums16");
   extern __shared__ __align__(16) unsigned char lds[];
   const int logical = xcd_logical_block(blockIdx.x, gridDim.x);
-  const int chunk = logical % C, b = logical / C;   // a sample's chunks on one XCD, as above
+  const int b = logical % B, chunk = logical / B;
   if (w.status[b]) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int Lp = m.L_pad, L = w.nlay[b];
-  constexpr int NS = n_sums(S);
-  const int ld = Lp + 1;                              // padded row length (doubles)
-  double* s_dt = reinterpret_cast<double*>(lds);      // dtau [nu][ld]
-  double* s_tb = s_dt + TILE * ld;                    // tau_bar [nu][ld], later dtau_bar
-  double* s_sums = s_tb + TILE * ld;                  // [Lp][NS]
-  const bool act = lane < TILE;                       // this lane holds a wavenumber of the tile
-  for (int i = tid; i < Lp * NS; i += kBlockT) s_sums[i] = 0.0;
+  const int Lp = m.L_pad, L = w.nlay[b], MB = (L + 15) >> 4, R = rows16(m.L_max);
+  double* s_dt = reinterpret_cast<double*>(lds);   // dtau, later dtau_bar [l][ld]
+  double* s_tb = s_dt + R * ld;                    // tau_bar [i][ld]
+  double* s_sums = s_tb + R * ld;                  // [R][16]
+  double* s_g = s_sums + R * 16;                   // [kWaves][64] non-grey cloud: sum_l D_l dtau_bar_l of a wave's layers
+  double* s_hq = s_g + kWaves * 64;                // [kCloudSpec][64] its sums over nu of G(nu) dQ/dp_k, G summed over the layers
+  double* s_area = s_hq + kCloudSpec * 64;         // [R]
+  int* s_live = reinterpret_cast<int*>(s_area + R);   // row blocks with a chord that is not opaque
+  const bool act = lane < TILE;                    // this lane holds a wavenumber of the tile
+  for (int i = tid; i < R * 16; i += kBlockT) s_sums[i] = 0.0;
 
   const double* rec = reinterpret_cast<const double*>(w.rec) + (size_t)b * Lp * rec_len(S);
   const int32_t* cells = w.cells + (size_t)b * Lp;
   const double* pm = w.pm64 + (size_t)b * Lp * Lp;
   const double* area = reinterpret_cast<const double*>(w.area) + (size_t)b * Lp;
+  for (int i = tid; i < R; i += kBlockT) s_area[i] = area[i];
   const double* dm = w.dm + (size_t)b * m.K;
 
-  double abar_r[ROWS];
-#pragma unroll
-  for (int k = 0; k < ROWS; ++k) abar_r[k] = 0.0;
-  // 16x16 Pbar tiles with column block >= row block, round-robin over waves
-  const int MB16 = (L + 15) >> 4;
-  int pt_mi[PSLOTS], pt_nl[PSLOTS];
+  // row blocks of the chord (t) and dtau_bar (d) products of this wave's column block, and
+  // its Pbar tiles (column block >= row block, round-robin over the waves)
+  const int h = lane >> 4, n16 = lane & 15, nb = wv % kNb, part = wv / kNb;
+  int t_mi[kSlots], d_ml[kSlots], pt_mi[kPSlots], pt_nl[kPSlots];
   {
-    int t = 0;
-    for (int q = 0; q < PSLOTS; ++q) pt_mi[q] = pt_nl[q] = -1;
-    for (int mi = 0; mi < MB16; ++mi)
-      for (int nl = mi; nl < MB16; ++nl, ++t)
-        if (t % 8 == wv && t / 8 < PSLOTS) {
-          pt_mi[t / 8] = mi;
-          pt_nl[t / 8] = nl;
-        }
-  }
-  f64x4 pacc[PSLOTS];
+    const unsigned mine_t = split_blocks16(part, kParts, MB, false), mine_d = split_blocks16(part, kParts, MB, true);
 #pragma unroll
-  for (int q = 0; q < PSLOTS; ++q) pacc[q] = f64x4{0.0, 0.0, 0.0, 0.0};
+    for (int q = 0; q < kSlots; ++q) {
+      t_mi[q] = __builtin_amdgcn_readfirstlane(nth_bit(mine_t, q));
+      d_ml[q] = __builtin_amdgcn_readfirstlane(nth_bit(mine_d, q));
+    }
+    int t = 0;
+    for (int q = 0; q < kPSlots; ++q) pt_mi[q] = pt_nl[q] = -1;
+    for (int mi = 0; mi < MB; ++mi)
+      for (int nl = mi; nl < MB; ++nl, ++t)
+        if (t % kWaves == wv && t / kWaves < kPSlots) {
+          pt_mi[t / kWaves] = mi;
+          pt_nl[t / kWaves] = nl;
+        }
+#pragma unroll
+    for (int q = 0; q < kPSlots; ++q) {
+      pt_mi[q] = __builtin_amdgcn_readfirstlane(pt_mi[q]);
+      pt_nl[q] = __builtin_amdgcn_readfirstlane(pt_nl[q]);
+    }
+  }
+  f64x4 abar_acc[kSlots], pacc[kPSlots];
+#pragma unroll
+  for (int q = 0; q < kSlots; ++q) abar_acc[q] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int q = 0; q < kPSlots; ++q) pacc[q] = f64x4{0.0, 0.0, 0.0, 0.0};
 
-  // non-grey cloud: Q_ext(nu) and its spectral derivatives, and (wave 0) the sums over
-  // nu of G(nu) dQ/dp_k with G = sum_l D_l dtau_bar_l
-  double hq[kCloudSpec] = {};
-  CloudCoef<double> cc{};
-  if (m.cloud_ng) cc = load_cloud<double>(w.cloud + (size_t)b * kCloudSpec);
+  if (m.cloud_ng && wv == 0)
+    for (int k = 0; k < kCloudSpec; ++k) s_hq[k * 64 + lane] = 0.0;
+  auto q_ext = [&](int nu, double* dq) {
+    return cloud_q<double>(m.cloud_qext, load_cloud<double>(w.cloud + (size_t)b * kCloudSpec), m.nu[nu], dq);
+  };
   const int ntiles = m.n_nu_pad / TILE;
   const int t0 = chunk * ntiles / C, t1 = (chunk + 1) * ntiles / C;
   for (int tile = t0; tile < t1; ++tile) {
     const int nu = tile * TILE + (act ? lane : 0);
     const double nu4 = tb.nu4d[nu];
-    double dqx[kCloudSpec];
-    const double qx = m.cloud_ng ? cloud_q<double>(m.cloud_qext, cc, m.nu[nu], dqx) : 1.0;
-    for (int l = wv; l < Lp; l += 8) {
-      double d = 0.0;
-      if (l < L && act) opacity_fp64_terms<S, CIA>(m, tb, cells[l], rec + (size_t)l * rec_len(S), nu, nu4, d, nullptr, nullptr, qx);
-      if (act) s_dt[lane * ld + l] = d;
-    }
-    const int bin = w.bin_of[nu];
-    const double dbar = bin >= 0 && act ? dm[bin] * w.inv_cnt[bin] : 0.0;
-    __syncthreads();
-    // tau_i, seeds, tau_bar
-#pragma unroll
-    for (int k = 0; k < ROWS; ++k) {
-      const int i = wv + 8 * k;
-      if (i < Lp) {
-        double tbv = 0.0;
-        if (i < L && act) {
-          double tau = 0.0;
-          for (int l = i; l < L; ++l) tau = fma(pm[(size_t)i * Lp + l], s_dt[lane * ld + l], tau);
-          const double one_m_e = -expm1(-tau);
-          abar_r[k] += dbar * one_m_e;
-          tbv = dbar * area[i] * (1.0 - one_m_e);
+    const double qx = m.cloud_ng ? q_ext(nu, nullptr) : 1.0;
+    // ---- optical depths
+    if (tid < kMaxBlocks16) s_live[tid] = 0;
+    {
+      LayerRows64<S, CIA> rows;
+      int cell_prev = -1;
+      for (int l = L * wv / kWaves; l < L * (wv + 1) / kWaves; ++l) {
+        const int cl = cells[l];
+        if (cl != cell_prev) {
+          fetch_rows64<S, CIA>(m, tb, cl, nu, rows);
+          cell_prev = cl;
         }
-        if (act) s_tb[lane * ld + i] = tbv;
+        const double d = eval_rows64<S, CIA>(rec + (size_t)l * rec_len(S), rows, nu4, qx);
+        if (act) s_dt[l * ld + lane] = d > 1.0e300 ? 1.0e300 : d;   // finite, as in the forward kernel
       }
     }
+    for (int l = L + wv; l < 16 * MB; l += kWaves)
+      if (act) s_dt[l * ld + lane] = 0.0;
     __syncthreads();
-    // Pbar += tau_bar dtau^T (FP64 MFMA, k = wavenumber)
+    // ---- chords, seeds, tau_bar
+    {
+      const int nu_c = tile * TILE + 16 * nb + n16;
+      const int bin = w.bin_of[nu_c];
+      const double dbar = bin >= 0 ? dm[bin] * w.inv_cnt[bin] : 0.0;
+      const double* pb = s_dt + 4 * h * ld + 16 * nb + n16;
 #pragma unroll
-    for (int q = 0; q < PSLOTS; ++q) {
-      const int mi = pt_mi[q], nl = pt_nl[q];
-      if (mi < 0) continue;
-      const int ri = 16 * mi + (lane & 15), cl = 16 * nl + (lane & 15);
+      for (int q = 0; q < kSlots; ++q) {
+        const int mi = t_mi[q];
+        if (mi < 0) continue;
+        const double* pa = pm + (size_t)(16 * mi + n16) * Lp + 4 * h;
+        f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+        f64x4 a = *reinterpret_cast<const f64x4*>(pa + 16 * mi);
 #pragma unroll 1
-      for (int ks = 0; ks < TILE / 4; ++ks) {
-        const int nr = 4 * ks + (lane >> 4);
-        pacc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(s_tb[nr * ld + ri], s_dt[nr * ld + cl], pacc[q], 0, 0, 0);
+        for (int K = mi; K < MB; ++K) {
+          const f64x4 cur = a;
+          if (K + 1 < MB) a = *reinterpret_cast<const f64x4*>(pa + 16 * (K + 1));
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(cur[j], pb[(16 * K + j) * ld], acc, 0, 0, 0);
+        }
+        bool live = false;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int i = 16 * mi + h + 4 * e;
+          const double tau = acc[e], ex = exp_neg_d(tau);
+          abar_acc[q][e] = fma(dbar, 1.0 - ex, abar_acc[q][e]);
+          s_tb[i * ld + 16 * nb + n16] = dbar * s_area[i] * ex;
+          live |= !(ex == 0.0);
+        }
+        if (__builtin_amdgcn_ballot_w64(live) != 0 && lane == 0) s_live[mi] = 1;
       }
     }
-    // dtau_bar_l = sum_{i <= l} P_il tau_bar_i
-    double dtb[ROWS];
+    __syncthreads();
+    int mi0 = 0;
+    while (mi0 < MB && !s_live[mi0]) ++mi0;
+    mi0 = __builtin_amdgcn_readfirstlane(mi0);
+    // ---- Pbar += tau_bar dtau^T (k = wavenumber)
 #pragma unroll
-    for (int k = 0; k < ROWS; ++k) {
-      const int l = wv + 8 * k;
-      double acc = 0.0;
-      if (l < L && act)
-        for (int i = 0; i <= l; ++i) acc = fma(pm[(size_t)i * Lp + l], s_tb[lane * ld + i], acc);
-      dtb[k] = acc;
+    for (int q = 0; q < kPSlots; ++q) {
+      const int mi = pt_mi[q], nl = pt_nl[q];
+      if (mi < mi0) continue;   // also the empty slots (mi = -1)
+      const double* pa = s_tb + (16 * mi + n16) * ld + h;
+      const double* pb = s_dt + (16 * nl + n16) * ld + h;
+#pragma unroll 4
+      for (int ks = 0; ks < TILE / 4; ++ks)
+        pacc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(pa[4 * ks], pb[4 * ks], pacc[q], 0, 0, 0);
+    }
+    __syncthreads();   // every reader of the optical depths is done: dtau_bar replaces them
+    // ---- dtau_bar = P^T tau_bar: rows l, k = chords mi0.. up to the block's own
+#pragma unroll
+    for (int q = 0; q < kSlots; ++q) {
+      const int ml = d_ml[q];
+      if (ml < mi0) continue;
+      const double* pa = pm + (size_t)(4 * h) * Lp + 16 * ml + n16;
+      const double* pb = s_tb + 4 * h * ld + 16 * nb + n16;
+      f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+      double a[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) a[j] = pa[(size_t)(16 * mi0 + j) * Lp];
+#pragma unroll 1
+      for (int K = mi0; K <= ml; ++K) {
+        double cur[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) cur[j] = a[j];
+        if (K < ml) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) a[j] = pa[(size_t)(16 * (K + 1) + j) * Lp];
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(cur[j], pb[(16 * K + j) * ld], acc, 0, 0, 0);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s_dt[(16 * ml + h + 4 * e) * ld + 16 * nb + n16] = acc[e];
     }
     __syncthreads();
+    // ---- per-layer sums
+    double g = 0.0;
+    {
+      const int lo = min(16 * mi0, L), n = L - lo;
+      LayerRows64<S, CIA> rows;
+      int cell_prev = -1;
+      for (int l = lo + n * wv / kWaves; l < lo + n * (wv + 1) / kWaves; ++l) {
+        const double db = act ? s_dt[l * ld + lane] : 0.0;
+        if (__builtin_amdgcn_ballot_w64(!(db == 0.0)) == 0) continue;
+        const int cl = cells[l];
+        if (cl != cell_prev) {
+          fetch_rows64<S, CIA>(m, tb, cl, nu, rows);
+          cell_prev = cl;
+        }
+        const double* rl = rec + (size_t)l * rec_len(S);
+        double t[S + 2], dw[S + 2], v[16];
+        eval_rows64_deriv<S, CIA>(rl, rows, t, dw);
 #pragma unroll
-    for (int k = 0; k < ROWS; ++k) {
-      const int l = wv + 8 * k;
-      if (l < Lp && act) s_tb[lane * ld + l] = dtb[k];
+        for (int k = 0; k < 16; ++k) v[k] = 0.0;
+        double ht = 0.0, htc = 0.0;
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+          v[s] = db * t[s];
+          ht = fma(t[s], dw[s], ht);
+        }
+        v[S] = db * ht;
+        if constexpr (CIA) {
+#pragma unroll
+          for (int p = 0; p < 2; ++p) {
+            v[S + 1 + p] = db * t[S + p];
+            htc = fma(t[S + p], dw[S + p], htc);
+          }
+          v[S + 3] = db * htc;
+        }
+        v[S + 4] = db * nu4;
+        v[S + 5] = db * qx;   // the cloud column: Q_ext weights the non-grey cloud (1 for the grey deck)
+        g = fma(rl[4], db, g);
+        const double tot = wave_sums16(v, lane);
+        if ((lane & 3) == 0) s_sums[l * 16 + (lane >> 2)] += tot;
+      }
     }
+    if (m.cloud_ng) s_g[wv * 64 + lane] = g;
     __syncthreads();
     if (m.cloud_ng && wv == 0) {
-      double g = 0.0;
-      if (act)
-        for (int l = 0; l < L; ++l) g = fma(rec[(size_t)l * rec_len(S) + 4], s_tb[lane * ld + l], g);
+      double gs = 0.0, dqx[kCloudSpec];
+      for (int k = 0; k < kWaves; ++k) gs += s_g[k * 64 + lane];
+      q_ext(nu, dqx);
 #pragma unroll
-      for (int k = 0; k < kCloudSpec; ++k) hq[k] = fma(g, dqx[k], hq[k]);
+      for (int k = 0; k < kCloudSpec; ++k) s_hq[k * 64 + lane] = fma(gs, dqx[k], s_hq[k * 64 + lane]);
     }
-    // per-layer sums
-    for (int l = wv; l < L; l += 8) {
-      double d, t[S + 2], dw[S + 2];
-      opacity_fp64_terms<S, CIA>(m, tb, cells[l], rec + (size_t)l * rec_len(S), nu, nu4, d, t, dw, qx);
-      const double db = act ? s_tb[lane * ld + l] : 0.0;
-      double sums[NS];
-      double ht = 0.0, htc = 0.0;
-#pragma unroll
-      for (int s = 0; s < S; ++s) {
-        sums[s] = db * t[s];
-        ht += db * t[s] * dw[s];
-      }
-      sums[S] = ht;
-      if (CIA) {
-#pragma unroll
-        for (int p = 0; p < 2; ++p) {
-          sums[S + 1 + p] = db * t[S + p];
-          htc += db * t[S + p] * dw[S + p];
-        }
-      } else {
-        sums[S + 1] = sums[S + 2] = 0.0;
-      }
-      sums[S + 3] = htc;
-      sums[S + 4] = db * nu4;
-      sums[S + 5] = db * qx;   // the cloud column: Q_ext weights the non-grey cloud (1 for the grey deck)
-#pragma unroll
-      for (int k = 0; k < NS; ++k) {
-        const double tot = wave_sum(sums[k]);
-        if (lane == 0) s_sums[l * NS + k] += tot;
-      }
-    }
-    __syncthreads();
   }
 
   const size_t pair = (size_t)b * C + chunk;
   double* ls = aw.layer_sums + pair * Lp * NS;
-  for (int i = tid; i < Lp * NS; i += kBlockT) ls[i] = s_sums[i];
+  for (int i = tid; i < Lp * NS; i += kBlockT) {
+    const int l = i / NS, k = i - l * NS;
+    ls[i] = l < L ? s_sums[l * 16 + k] : 0.0;
+  }
   if (m.cloud_ng && wv == 0) {
 #pragma unroll
     for (int k = 0; k < kCloudSpec; ++k) {
-      const double tot = wave_sum(hq[k]);
+      const double tot = wave_sum(s_hq[k * 64 + lane]);
       if (lane == 0) aw.hq64[pair * kCloudSpec + k] = tot;
     }
   }
   double* pb = reinterpret_cast<double*>(aw.pbar) + pair * Lp * Lp;
 #pragma unroll
-  for (int q = 0; q < PSLOTS; ++q) {
+  for (int q = 0; q < kPSlots; ++q) {
     const int mi = pt_mi[q], nl = pt_nl[q];
     if (mi < 0) continue;
 #pragma unroll
-    // v_mfma_f64_16x16x4f64 result: D[i][j] at lane j + 16 (i % 4), element i / 4
-    for (int j = 0; j < 4; ++j) pb[(size_t)(16 * mi + (lane >> 4) + 4 * j) * Lp + 16 * nl + (lane & 15)] = pacc[q][j];
+    for (int e = 0; e < 4; ++e) pb[(size_t)(16 * mi + h + 4 * e) * Lp + 16 * nl + n16] = pacc[q][e];
   }
-  double* ab = aw.abar + pair * Lp;
+  // abar: over the 16 columns of a block, then over the column blocks
+  __syncthreads();
+  double* s_ab = s_dt;   // [kNb][R]
 #pragma unroll
-  for (int k = 0; k < ROWS; ++k) {
-    const int i = wv + 8 * k;
-    const double v = wave_sum(abar_r[k]);
-    if (lane == 0 && i < Lp) ab[i] = v;
+  for (int q = 0; q < kSlots; ++q) {
+    const int mi = t_mi[q];
+    if (mi < 0) continue;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      double v = abar_acc[q][e];
+#pragma unroll
+      for (int off = 8; off > 0; off >>= 1) v += __shfl_xor(v, off);
+      if (n16 == 0) s_ab[nb * R + 16 * mi + h + 4 * e] = v;
+    }
+  }
+  __syncthreads();
+  double* ab = aw.abar + pair * Lp;
+  for (int i = tid; i < Lp; i += kBlockT) {
+    double v = 0.0;
+    if (i < L)
+#pragma unroll
+      for (int k = 0; k < kNb; ++k) v += s_ab[k * R + i];
+    ab[i] = v;
   }
 }
 
@@ -1437,9 +1550,23 @@ static int adj_slots(int variant) {
 
 int adjoint_chunks(const Model& m, const AdjWork& aw, int B, bool fp64) {
   if (m.mode == kEmission) return 1;   // the emission reverse pass keeps no per-chunk partials
-  // the FP64 reverse kernel walks 64-wavenumber tiles
   const int tiles = m.n_nu_pad / (fp64 ? adj_tile64(m) : adj_tile(aw.variant));
-  const int target = fp64 ? 1024 : aw.chunk_target;
+  if (fp64) {
+    // one workgroup per CU at a time: of the splits into at most 1024 work items, the one
+    // whose rounds over the chip take the fewest tiles in a row (the coarsest of equals)
+    const int cus = 256, cmax = std::min(std::max(1024 / B, 1), tiles);
+    int best = 1;
+    long cost = LONG_MAX;
+    for (int c = 1; c <= cmax; ++c) {
+      const long v = (long)((B * (long)c + cus - 1) / cus) * ((tiles + c - 1) / c);
+      if (v < cost) {
+        cost = v;
+        best = c;
+      }
+    }
+    return best;
+  }
+  const int target = aw.chunk_target;
   int c = (target + B - 1) / B;
   return c < 1 ? 1 : (c > tiles ? tiles : c);
 }
@@ -1527,8 +1654,11 @@ bool adjoint_alloc(AdjWork& aw, const Model& m, int B_max, bool fp64, const std:
 }
 
 static size_t adj_lds_bytes(const Model& m, bool fp64, int variant) {
-  const size_t Lp = m.L_pad, ns = n_sums(m.S);
-  if (fp64) return (size_t)2 * adj_tile64(m) * (Lp + 1) * 8 + Lp * ns * 8;
+  const size_t Lp = m.L_pad;
+  if (fp64) {
+    const size_t R = rows16(m.L_max);
+    return (R * (2 * (adj_tile64(m) + 2) + 16 + 1) + (kBlockT / 64 + kCloudSpec) * 64) * 8 + kMaxBlocks16 * 4;
+  }
   const size_t tile = adj_tile(variant), rows = std::min(Lp, (size_t)32 * adj_mb(variant));
   return std::max(2 * tile * (32 * adj_mb(variant) + 4) * 4 + rows * 4, tile / 32 * Lp * 8);
 }
@@ -1546,7 +1676,7 @@ const void* adj_mixed_kernel(int variant) {
 template <bool F64, int S, bool CIA>
 const void* adj_kernel(int variant) {
   if constexpr (F64)
-    return variant == 0 ? (const void*)k_trans_adj_fp64<S, CIA, 64, 16, 5> : (const void*)k_trans_adj_fp64<S, CIA, 32, 20, 7>;
+    return variant == 0 ? (const void*)k_trans_adj_fp64<S, CIA, 64> : (const void*)k_trans_adj_fp64<S, CIA, 32>;
   else return adj_mixed_kernel<S, CIA>(variant);
 }
 
