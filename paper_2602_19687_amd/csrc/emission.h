@@ -1,5 +1,6 @@
 #pragma once
-#include "common.h"
+#include "kernels.h"
+#include "opacity.h"
 
 namespace exofwd {
 // dtau_out (may be null): layer optical depths [B][L_pad][n_nu_pad] for the reverse pass, float in reduced
@@ -7,7 +8,6 @@ namespace exofwd {
 void launch_emission(const Model& m, const Work& w, const Tables& tb, int B, void* spec, bool fp64, hipStream_t st,
                      void* dtau_out = nullptr);
 hipError_t emission_configure(const Model& m, bool fp64);
-size_t emission_lds_bytes(const Model& m, bool fp64);
 
 // Planck intensity per unit wavenumber, 2 h c^2 nu^3 / (e^y - 1) with y = h c nu / k T,
 // from c1n3 = 2 h c^2 nu^3, c2n_log2e = log2(e) h c nu / k and inv_t = 1/T; em1
@@ -43,6 +43,24 @@ __device__ inline void slab_terms(float x, float e, float& om, float& src) {
     om = 1.0f - e;
     src = om * __builtin_amdgcn_rcpf(x) - e;
   }
+}
+
+// ---- plain FP64 forms (opacity.h: exp2m1_d, rcp_d)
+// Planck intensity 2 h c^2 nu^3 / (e^y - 1), y = h c nu / k T, from c1n3 = 2 h c^2 nu^3 and
+// y2 = y log2(e); em1 returns e^y - 1
+__device__ inline double planck_d(double c1n3, double y2, double& em1) {
+  double e;
+  exp2m1_d(fmin(y2, 1000.0), em1, e);   // past 2^1000 the intensity is zero beside any other
+  return c1n3 * rcp_d(em1);
+}
+// e = e^-x, om = 1 - e^-x and src = (1 - e^-x)/x - e^-x, by its series below x = 1e-4, for
+// x >= 0; r = 1 / x (unused below 1e-4)
+__device__ inline void slab_d(double x, double& e, double& om, double& src, double& r) {
+  double em1;
+  exp2m1_d(fmax(-1.4426950408889634074 * x, -1000.0), em1, e);
+  om = -em1;
+  r = rcp_d(x);
+  src = x < 1.0e-4 ? x * (0.5 + x * (-1.0 / 3.0 + x * (0.125 + x * (-1.0 / 30.0)))) : fma(om, r, -e);
 }
 
 }  // namespace exofwd

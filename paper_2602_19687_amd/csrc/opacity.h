@@ -277,11 +277,9 @@ __device__ inline void frag_hl(const uint32_t* x, bf16x8& hi, bf16x8& lo) {
 // ---------------------------------------------------------------------------
 // Plain FP64 form: log10 sigma tables read as they are, one wavenumber per lane.
 
-// 2^x for finite x (0 or infinity past the exponent range): the fractional part, in
-// [-1/2, 1/2], through a degree-11 polynomial (1 + f q(f), q interpolating (2^f - 1)/f
-// at the Chebyshev points of the interval; 2e-17 relative)
-__device__ inline double exp2_d(double x) {
-  const double n = __builtin_rint(x), f = x - n;
+// (2^f - 1) / f on [-1/2, 1/2], interpolated at the Chebyshev points of the interval: then
+// 1 + f q(f) is 2^f to 2e-17 relative
+__device__ inline double exp2_q(double f) {
   double q = 4.4549605981865186e-10;
   q = fma(q, f, 7.072585949269223e-09);
   q = fma(q, f, 1.0178062445845774e-07);
@@ -292,8 +290,25 @@ __device__ inline double exp2_d(double x) {
   q = fma(q, f, 0.009618129107606888);
   q = fma(q, f, 0.0555041086648216);
   q = fma(q, f, 0.24022650695910097);
-  q = fma(q, f, 0.6931471805599453);
-  return __builtin_ldexp(fma(q, f, 1.0), (int)n);
+  return fma(q, f, 0.6931471805599453);
+}
+// 2^x for finite x (0 or infinity past the exponent range)
+__device__ inline double exp2_d(double x) {
+  const double n = __builtin_rint(x), f = x - n;
+  return __builtin_ldexp(fma(exp2_q(f), f, 1.0), (int)n);
+}
+// e = 2^x and em1 = 2^x - 1, which keeps its digits where x is small, for |x| <= 1022
+__device__ inline void exp2m1_d(double x, double& em1, double& e) {
+  const double n = __builtin_rint(x), f = x - n;
+  const double t = f * exp2_q(f), s = __builtin_ldexp(1.0, (int)n);
+  em1 = fma(s, t, s - 1.0);
+  e = fma(s, t, s);
+}
+// 1 / x to the last digit or two (x and 1 / x normal): two Newton steps
+__device__ inline double rcp_d(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(fma(-x, r, 1.0), r, r);
+  return fma(fma(-x, r, 1.0), r, r);
 }
 // e^-tau for tau >= 0 (infinite included; a NaN stays one)
 __device__ inline double exp_neg_d(double tau) {
