@@ -30,17 +30,6 @@ __device__ inline float2 ld_stream2(const float* p) {
   return make_float2(v.x, v.y);
 }
 
-__device__ inline float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-  return v;
-}
-__device__ inline double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-  return v;
-}
-
 // cost-balanced split of 32-row blocks between `parts` (2 or 4) waves: each block in
 // turn goes to the part with the least cost so far (the lowest such part on a tie);
 // `rev` costs rows by their K extent in the transposed product (grows with the
@@ -600,13 +589,12 @@ __global__ __launch_bounds__(kBlock) void k_layer_sums_mixed(Model m, Work w, Ta
   float* out = aw.lsum + ((size_t)b * aw.lsum_stride + chunk) * Lp * NS;
 #pragma unroll
   for (int q = 0; q < kLs; ++q) {
-    const int l = l0 + q;
     if (q >= cnt) continue;
+    float v[16];
 #pragma unroll
-    for (int k = 0; k < NS; ++k) {
-      const float tot = wave_sum(acc[q][k]);
-      if (lane == 0) out[(size_t)l * NS + k] = tot;
-    }
+    for (int k = 0; k < 16; ++k) v[k] = k < NS ? acc[q][k < NS ? k : 0] : 0.0f;
+    const float tot = wave_sums16(v, lane);
+    if ((lane & 3) == 0 && (lane >> 2) < NS) out[(size_t)(l0 + q) * NS + (lane >> 2)] = tot;
   }
 }
 
@@ -643,7 +631,7 @@ __global__ __launch_bounds__(kBlock) void k_cloud_spectral(Model m, Work w, AdjW
   }
 #pragma unroll
   for (int k = 0; k < kCloudSpec; ++k) {
-    const float tot = wave_sum(hq[k]);
+    const float tot = wave_sum_all(hq[k]);
     if (lane == 0) aw.hq[((size_t)b * aw.lsum_stride + chunk) * kCloudSpec + k] = tot;
   }
 }
@@ -651,51 +639,6 @@ __global__ __launch_bounds__(kBlock) void k_cloud_spectral(Model m, Work w, AdjW
 // ============================================================================
 // FP64 reverse kernel: 512 threads, one sample and wavenumber chunk per workgroup, every
 // product on v_mfma_f64_16x16x4f64
-
-template <int CTRL>
-__device__ inline double dpp_move(double v) {
-  const uint64_t u = (uint64_t)__double_as_longlong(v);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)u, CTRL, 0xF, 0xF, true);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), CTRL, 0xF, 0xF, true);
-  return __longlong_as_double((long long)((uint64_t)lo | ((uint64_t)hi << 32)));
-}
-
-// a + b after the halves (ROW16: the odd 16-lane rows) of a and the other halves of b
-// changed places: lanes of the lower half get their a plus the upper half's a, lanes of
-// the upper half both halves' b
-template <bool ROW16>
-__device__ inline double swap_add(double a, double b) {
-  const uint64_t ua = (uint64_t)__double_as_longlong(a), ub = (uint64_t)__double_as_longlong(b);
-  auto sw = [](uint32_t x, uint32_t y) {
-    if constexpr (ROW16) return __builtin_amdgcn_permlane16_swap(x, y, false, false);
-    else return __builtin_amdgcn_permlane32_swap(x, y, false, false);
-  };
-  const auto lo = sw((uint32_t)ua, (uint32_t)ub), hi = sw((uint32_t)(ua >> 32), (uint32_t)(ub >> 32));
-  return __longlong_as_double((long long)((uint64_t)lo[0] | ((uint64_t)hi[0] << 32))) +
-         __longlong_as_double((long long)((uint64_t)lo[1] | ((uint64_t)hi[1] << 32)));
-}
-
-// Sums over the wave of 16 values per lane at once: the lanes of quad n (n = lane / 4) get
-// the sum of v[n].  Halving exchanges, about 60 instructions where a butterfly for each
-// value would take 18 each.
-__device__ inline double wave_sums16(double (&v)[16], int lane) {
-  double a[8], b[4], c[2];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) a[i] = swap_add<false>(v[i], v[i + 8]);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) b[i] = swap_add<true>(a[i], a[i + 4]);
-  const bool k8 = lane & 8, k4 = lane & 4;
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {   // row_ror:8, the other eight lanes of the row
-    const double keep = k8 ? b[i + 2] : b[i], send = k8 ? b[i] : b[i + 2];
-    c[i] = keep + dpp_move<0x128>(send);
-  }
-  const double keep = k4 ? c[1] : c[0], send = k4 ? c[0] : c[1];
-  double r = keep + dpp_move<0x141>(send);   // row_half_mirror: the other quad of the eight
-  r += dpp_move<0xB1>(r);                    // quad_perm [1,0,3,2], then [2,3,0,1]
-  r += dpp_move<0x4E>(r);
-  return r;
-}
 
 // Per tile: the layer optical depths (each wave a contiguous run of layers) -> LDS; the
 // chords, seeds and tau_bar -> LDS; the path-matrix adjoint (accumulated in registers over
@@ -941,7 +884,7 @@ __global__ __launch_bounds__(kBlockT) void k_trans_adj_fp64(Model m, Work w, Tab
   if (m.cloud_ng && wv == 0) {
 #pragma unroll
     for (int k = 0; k < kCloudSpec; ++k) {
-      const double tot = wave_sum(s_hq[k * 64 + lane]);
+      const double tot = wave_sum_all(s_hq[k * 64 + lane]);
       if (lane == 0) aw.hq64[pair * kCloudSpec + k] = tot;
     }
   }

@@ -21,12 +21,6 @@
 
 namespace exofwd {
 
-__device__ inline float wave_sum_f(float v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-  return v;
-}
-
 // d src / dx of src = (1 - e^-x)/x - e^-x (series below x = 0.1 as in slab_terms)
 __device__ inline float slab_dsrc(float x, float e, float om) {
   if (x < 0.1f)
@@ -117,13 +111,13 @@ __global__ __launch_bounds__(kBlock) void k_emis_adj_mixed(Model m, Work w, AdjW
       inten[k] = fmaf(om, b_top - inten[k], fmaf(db, src, inten[k]));
     }
     __builtin_nontemporal_store(dsum, &dtb[(size_t)l * npad]);   // read once, by the layer sums
-    const float lev = wave_sum_f(bb_lev * dbdt_bot);
+    const float lev = wave_sum_all(bb_lev * dbdt_bot);
     if (lane == 0) ps[l] = lev;
     bb_lev = bt_bar;
     b_bot = b_top;
     dbdt_bot = dbdt_top;
   }
-  const float lev_top = wave_sum_f(bb_lev * dbdt_bot);
+  const float lev_top = wave_sum_all(bb_lev * dbdt_bot);
   if (lane == 0) ps[L] = lev_top;
 }
 
@@ -248,11 +242,11 @@ __global__ __launch_bounds__(kBlock) void k_layer_sums_emis(Model m, Work w, Tab
 #pragma unroll
   for (int q = 0; q < kLayers; ++q) {
     if (q >= cnt) continue;
+    float v[16];
 #pragma unroll
-    for (int k = 0; k < NS; ++k) {
-      const float tot = wave_sum_f(acc[q][k]);
-      if (lane == 0) out[(size_t)(l0 + q) * NS + k] = tot;
-    }
+    for (int k = 0; k < 16; ++k) v[k] = k < NS ? acc[q][k < NS ? k : 0] : 0.0f;
+    const float tot = wave_sums16(v, lane);
+    if ((lane & 3) == 0 && (lane >> 2) < NS) out[(size_t)(l0 + q) * NS + (lane >> 2)] = tot;
   }
 }
 
@@ -263,24 +257,6 @@ __global__ __launch_bounds__(kBlock) void k_layer_sums_emis(Model m, Work w, Tab
 // reciprocal for the three quotients of a slab, lane moves for the level sums, the next
 // layer's loads in flight), layer sums 2.66 -> 0.71 ms (sums in registers, entries fetched
 // once per cell and tile; the accumulators used to live in scratch memory)
-template <int CTRL>
-__device__ inline double dpp_d(double v) {
-  const uint64_t u = (uint64_t)__double_as_longlong(v);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)u, CTRL, 0xF, 0xF, true);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), CTRL, 0xF, 0xF, true);
-  return __longlong_as_double((long long)((uint64_t)lo | ((uint64_t)hi << 32)));
-}
-// sum over the wave (every lane gets it), by lane moves inside the rows of 16
-__device__ inline double wave_sum_d(double v) {
-  v += dpp_d<0xB1>(v);    // quad_perm [1,0,3,2]
-  v += dpp_d<0x4E>(v);    // quad_perm [2,3,0,1]
-  v += dpp_d<0x141>(v);   // row_half_mirror
-  v += dpp_d<0x128>(v);   // row_ror:8
-  v += __shfl_xor(v, 16);
-  v += __shfl_xor(v, 32);
-  return v;
-}
-
 __global__ __launch_bounds__(kBlock) void k_emis_adj_fp64(Model m, Work w, AdjWork aw, int B) {
   const int logical = xcd_logical_block(blockIdx.x, gridDim.x);
   const int b = logical % B;
@@ -353,7 +329,7 @@ __global__ __launch_bounds__(kBlock) void k_emis_adj_fp64(Model m, Work w, AdjWo
       inten[k] = fma(om, b_top - inten[k], fma(db, src, inten[k]));
     }
     __builtin_nontemporal_store(dsum, &dtb[(size_t)l * npad]);   // read once, by the layer sums
-    const double lev = wave_sum_d(bb_lev * dbdt_bot);
+    const double lev = wave_sum_all(bb_lev * dbdt_bot);
     if (lane == 0) ps[l] = lev;
     bb_lev = bt_bar;
     b_bot = b_top;
@@ -361,7 +337,7 @@ __global__ __launch_bounds__(kBlock) void k_emis_adj_fp64(Model m, Work w, AdjWo
     d = d_next;
     x_above = x_next;
   }
-  const double lev = wave_sum_d(bb_lev * dbdt_bot);
+  const double lev = wave_sum_all(bb_lev * dbdt_bot);
   if (lane == 0) ps[L] = lev;
 }
 
@@ -431,11 +407,11 @@ __global__ __launch_bounds__(kBlock) void k_layer_sums_emis_fp64(Model m, Work w
 #pragma unroll
   for (int q = 0; q < kLayers; ++q) {
     if (q >= cnt) continue;
+    double v[16];
 #pragma unroll
-    for (int k = 0; k < NS; ++k) {
-      const double tot = k < NA ? wave_sum_d(acc[q][k < NA ? k : 0]) : 0.0;
-      if (lane == 0) out[(size_t)(l0 + q) * NS + k] = tot;
-    }
+    for (int k = 0; k < 16; ++k) v[k] = k < NA ? acc[q][k < NA ? k : 0] : 0.0;
+    const double tot = wave_sums16(v, lane);
+    if ((lane & 3) == 0 && (lane >> 2) < NS) out[(size_t)(l0 + q) * NS + (lane >> 2)] = tot;
   }
 }
 

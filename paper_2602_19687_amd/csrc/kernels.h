@@ -25,6 +25,95 @@ __device__ inline int class_position(int s, int n_slots, int per_slot) {
   return (s % spx) * 8 + s / spx;
 }
 
+// ---- sums over a wave of 16 values per lane at once: the lanes of quad n (n = lane / 4) get
+// the sum of v[n].  Halving exchanges: each step a lane passes on the half of its values
+// that its partner keeps, so the 16 sums take about 40 instructions (FP32) where a
+// butterfly takes 12 and six LDS accesses for each.  The sums have the butterfly's tree
+// (lanes l ^ 32, then 16, 8, 4, 2, 1), bit for bit.
+template <int CTRL>
+__device__ inline uint32_t dpp_mov(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, true);
+}
+// the value of lane l ^ BIT (1, 2, 4 or 8)
+template <int BIT>
+__device__ inline uint32_t lane_xor(uint32_t v) {
+  if constexpr (BIT == 1) return dpp_mov<0xB1>(v);         // quad_perm [1,0,3,2]
+  else if constexpr (BIT == 2) return dpp_mov<0x4E>(v);    // quad_perm [2,3,0,1]
+  else if constexpr (BIT == 8) return dpp_mov<0x128>(v);   // row_ror:8
+  else {
+    const int up = __builtin_amdgcn_update_dpp(0, (int)v, 0x104, 0xF, 0x5, true);      // row_shl:4, quads 0 and 2
+    return (uint32_t)__builtin_amdgcn_update_dpp(up, (int)v, 0x114, 0xF, 0xA, true);   // row_shr:4, quads 1 and 3
+  }
+}
+template <int BIT>
+__device__ inline float lane_xor(float v) { return __uint_as_float(lane_xor<BIT>(__float_as_uint(v))); }
+template <int BIT>
+__device__ inline double lane_xor(double v) {
+  const uint64_t u = (uint64_t)__double_as_longlong(v);
+  const uint64_t lo = lane_xor<BIT>((uint32_t)u), hi = lane_xor<BIT>((uint32_t)(u >> 32));
+  return __longlong_as_double((long long)(lo | (hi << 32)));
+}
+// x and y after the upper half of x and the lower half of y (BIT 32; BIT 16: the odd rows
+// of x and the even rows of y) changed places
+template <int BIT>
+__device__ inline void lane_swap(uint32_t& x, uint32_t& y) {
+  if constexpr (BIT == 32) {
+    const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+    x = r[0];
+    y = r[1];
+  } else {
+    const auto r = __builtin_amdgcn_permlane16_swap(x, y, false, false);
+    x = r[0];
+    y = r[1];
+  }
+}
+// lanes with bit BIT of the lane clear: a + a of lane ^ BIT; set: the same for b
+template <int BIT>
+__device__ inline float halve_add(float a, float b) {
+  uint32_t x = __float_as_uint(a), y = __float_as_uint(b);
+  lane_swap<BIT>(x, y);
+  return __uint_as_float(x) + __uint_as_float(y);
+}
+template <int BIT>
+__device__ inline double halve_add(double a, double b) {
+  const uint64_t ua = (uint64_t)__double_as_longlong(a), ub = (uint64_t)__double_as_longlong(b);
+  uint32_t xl = (uint32_t)ua, xh = (uint32_t)(ua >> 32), yl = (uint32_t)ub, yh = (uint32_t)(ub >> 32);
+  lane_swap<BIT>(xl, yl);
+  lane_swap<BIT>(xh, yh);
+  return __longlong_as_double((long long)((uint64_t)xl | ((uint64_t)xh << 32))) +
+         __longlong_as_double((long long)((uint64_t)yl | ((uint64_t)yh << 32)));
+}
+template <typename T>
+__device__ inline T wave_sums16(const T (&v)[16], int lane) {
+  T a[8], b[4], c[2];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) a[i] = halve_add<32>(v[i], v[i + 8]);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) b[i] = halve_add<16>(a[i], a[i + 4]);
+  const bool k8 = lane & 8, k4 = lane & 4;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const T keep = k8 ? b[i + 2] : b[i], send = k8 ? b[i] : b[i + 2];
+    c[i] = keep + lane_xor<8>(send);
+  }
+  const T keep = k4 ? c[1] : c[0], send = k4 ? c[0] : c[1];
+  T r = keep + lane_xor<4>(send);
+  r += lane_xor<2>(r);
+  r += lane_xor<1>(r);
+  return r;
+}
+// sum over the wave, every lane gets it (the same tree)
+template <typename T>
+__device__ inline T wave_sum_all(T v) {
+  v += __shfl_xor(v, 32);
+  v += __shfl_xor(v, 16);
+  v += lane_xor<8>(v);
+  v += lane_xor<4>(v);
+  v += lane_xor<2>(v);
+  v += lane_xor<1>(v);
+  return v;
+}
+
 void launch_profile(const Model& m, const Work& w, int B, const double* params, const int32_t* n_layers,
                     bool fp64, hipStream_t st);
 // dtau_out (reduced precision only, may be null): layer optical depths [B][L_pad][n_nu_pad] for the reverse pass
