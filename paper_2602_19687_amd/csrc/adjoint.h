@@ -47,6 +47,8 @@ struct AdjWork {
   double* psum64;
   double* lsum64;      // [B_max][lsum_chunks][L_pad][n_sums]
   double* hq64;        // FP64 transmission, non-grey cloud: [pair][kCloudSpec] the sums of hq
+  double* lred;        // [B_max][L_pad][n_sums] the layer sums, added over the chunks
+  double* pred;        // emission: [B_max][L_pad+1] the per-level sums, added over the tiles
   int lsum_chunks;     // wavenumber chunks of the layer-sum kernel (n_tiles / ls_tiles, rounded up)
   int lsum_stride;     // allocated chunks per sample (the bound over the ls_tiles choices)
 };

@@ -924,15 +924,7 @@ __global__ __launch_bounds__(kBlockT) void k_trans_adj_fp64(Model m, Work w, Tab
 
 // ============================================================================
 // FP64 chain: one workgroup per sample
-__device__ inline void block_sum(double* s_red, int tid, int n) {
-  // s_red[n][kBlock]: tree over the second index, result in s_red[k][0]
-  for (int hh = kBlock / 2; hh > 0; hh >>= 1) {
-    __syncthreads();
-    if (tid < hh)
-      for (int k = 0; k < n; ++k) s_red[k * kBlock + tid] += s_red[k * kBlock + tid + hh];
-  }
-  __syncthreads();
-}
+constexpr int kBlockC = 512, kWavesC = kBlockC / 64;
 
 // derivatives of P_il with respect to r_l, r_{l+1} and b_i (l > i), or the
 // full derivatives with respect to r_i, r_{i+1} on the diagonal
@@ -949,11 +941,11 @@ __device__ inline void path_derivs(const double* r, int i, int l, double& d_lo, 
   const double bb = 0.5 * (r[i] + r[i + 1]);
   const double rup = r[l + 1], rlo = r[l];
   const double sup = sqrt((rup - bb) * (rup + bb)), slo = sqrt((rlo - bb) * (rlo + bb));
-  const double nn = 2.0 * (rup + rlo), den = sup + slo;
-  const double f = nn / (den * den);
-  d_up = 2.0 / den - f * rup / sup;
-  d_lo = 2.0 / den - f * rlo / slo;
-  d_b = f * bb * (1.0 / sup + 1.0 / slo);
+  const double iup = rcp_d(sup), ilo = rcp_d(slo), iden = rcp_d(sup + slo);
+  const double f = 2.0 * (rup + rlo) * iden * iden;
+  d_up = 2.0 * iden - f * rup * iup;
+  d_lo = 2.0 * iden - f * rlo * ilo;
+  d_b = f * bb * (iup + ilo);
 }
 
 // Slopes of the monotone cubic Hermite interpolant through (xk, yk) and their
@@ -1004,16 +996,46 @@ __device__ void pchip_slopes_jac(const double* xk, const double* yk, int n, doub
   d[n - 1] = end(n - 1, n - 2, n - 3);
 }
 
+// Inclusive running sums over n <= 192 values by one wave, three neighbours a lane:
+// out[i] = get(0) + ... + get(i), or with rev get(n - 1) + ... + get(i).
+template <typename Get>
+__device__ inline void wave_scan(int lane, int n, bool rev, Get get, double* out) {
+  double v[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const int q = 3 * lane + k;
+    v[k] = q < n ? get(rev ? n - 1 - q : q) : 0.0;
+  }
+  v[1] += v[0];
+  v[2] += v[1];
+  double t = v[2];
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const double u = __shfl_up(t, d);
+    if (lane >= d) t += u;
+  }
+  const double before = __shfl_up(t, 1);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const int q = 3 * lane + k;
+    if (q < n) out[rev ? n - 1 - q : q] = (lane > 0 ? before : 0.0) + v[k];
+  }
+}
+
+// Bound by latency (one workgroup per sample): sums over the block are 16 at a time (a wave
+// by halving exchanges, then the waves), the hydrostatic recursion is four scans, and the
+// chunks of every partial sum have been added by k_reduce_chunks.  One sample of 100
+// layers and 30000 wavenumbers: 157 -> 32 us (1024 samples 392 -> 123 us; 64 samples of up
+// to 150 layers and 400000 wavenumbers 728 -> 48 us), the chunk sums 58 -> 12 us.
 template <typename PbarT>
-__global__ __launch_bounds__(kBlock) void k_chain(Model m, Work w, AdjWork aw, int C, int Cn, const double* __restrict__ params,
-                                                  const uint8_t* __restrict__ mask, double* __restrict__ grad) {
-  const int b = blockIdx.x, tid = threadIdx.x;
-  const int Lp = m.L_pad;
-  const int NS = n_sums(m.S);
-  const int NT = sizeof(PbarT) == 8 ? NS : n_lsums(m);   // stride of the stored layer sums
+__global__ __launch_bounds__(kBlockC) void k_chain(Model m, Work w, AdjWork aw, int C, const double* __restrict__ params,
+                                                   const uint8_t* __restrict__ mask, double* __restrict__ grad) {
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int Lp = m.L_pad, S = m.S;
+  const int NS = n_sums(S);
   double* gout = grad + (size_t)b * m.P;
   if (w.status[b]) {
-    for (int k = tid; k < m.P; k += kBlock) gout[k] = 0.0;
+    for (int k = tid; k < m.P; k += kBlockC) gout[k] = 0.0;
     return;
   }
   const int L = w.nlay[b];
@@ -1021,98 +1043,107 @@ __global__ __launch_bounds__(kBlock) void k_chain(Model m, Work w, AdjWork aw, i
   const double* th = params + (size_t)real_sample(m, b) * m.P;
   const bool cloudy = m.has_cloud && !clear_sample(m, b);
   const bool ng = m.cloud_ng && cloudy;
-  __shared__ double s_r[kMaxLayers + 1], s_rb[kMaxLayers + 1], s_ub[kMaxLayers + 1];
+  const bool trans = m.mode == kTransmission;
+  constexpr int kMaxSeg = 8;
+  __shared__ double s_r[kMaxLayers + 1], s_ub[kMaxLayers + 1], s_scan[4][kMaxLayers + 1];
   __shared__ double s_t[kMaxLayers], s_tb[kMaxLayers], s_lndr[kMaxLayers];
-  __shared__ double s_clo[kMaxLayers], s_cup[kMaxLayers], s_bb[kMaxLayers];
-  __shared__ double s_red[16 * kBlock];
-  __shared__ double s_scal[8];
+  __shared__ double s_plo[kMaxSeg * kMaxLayers], s_pup[kMaxSeg * kMaxLayers], s_pb[kMaxSeg * kMaxLayers];
+  __shared__ double s_w[2][kWavesC][16], s_sum[2][16], s_x[kMaxSpecies];
+  __shared__ double s_kx[kMaxKnots], s_ky[kMaxKnots], s_kd[kMaxKnots], s_kj[kMaxKnots * kMaxKnots];
+  __shared__ int s_above;
 
   const double* rl = w.r_lev + (size_t)b * (Lp + 1);
   const double* tl = w.t_lay + (size_t)b * Lp;
-  for (int j = tid; j <= L; j += kBlock) s_r[j] = rl[j];
-  for (int l = tid; l < L; l += kBlock) s_t[l] = tl[l];
+  const double step = (m.log10_ptop - m.log10_pbot) / L;
+  const double ln10 = 2.302585092994045684017991454684;
+  const double dlnp = -step * ln10;
+  auto logp_lev = [&](int j) { return j == L ? m.log10_ptop : m.log10_pbot + j * step; };
+  const double lpref = log10(m.p_ref / kBar);
+  if (tid == 0) s_above = 0;
+  __syncthreads();
+  for (int j = tid; j <= L; j += kBlockC) {
+    s_r[j] = rl[j];
+    if (logp_lev(j) > lpref) atomicAdd(&s_above, 1);
+  }
+  for (int l = tid; l < L; l += kBlockC) s_t[l] = tl[l];
+  if (tid < S) s_x[tid] = exp10(th[m.n_tp + tid]);
+  if (m.tp_kind == kTpPchip && tid == 64) {
+    for (int k = 0; k < m.n_knots; ++k) {
+      s_kx[k] = m.n_knots == 1 ? m.log10_ptop : m.log10_ptop + k * ((m.log10_pbot - m.log10_ptop) / (m.n_knots - 1));
+      s_ky[k] = th[k];
+    }
+    s_kx[m.n_knots - 1] = m.log10_pbot;
+    pchip_slopes_jac(s_kx, s_ky, m.n_knots, s_kd, s_kj);
+  }
+  __syncthreads();
 
   // chemistry and constants (every thread)
-  double x[kMaxSpecies];
   double sx = 0.0;
-  for (int s = 0; s < m.S; ++s) { x[s] = exp10(th[m.n_tp + s]); sx += x[s]; }
+  for (int s = 0; s < S; ++s) sx += s_x[s];
   const double xh2 = (1.0 - sx) / (1.0 + kHeH2), xhe = kHeH2 * xh2;
   const bool mu_free = !(m.mu_fixed > 0.0);
   double mu = m.mu_fixed;
   if (mu_free) {
     mu = xh2 * kMH2 + xhe * kMHe;
-    for (int s = 0; s < m.S; ++s) mu += x[s] * m.mass[s];
+    for (int s = 0; s < S; ++s) mu += s_x[s] * m.mass[s];
   }
   const double scale = m.has_scale ? th[m.idx_scale] : 1.0;
   const double g_ref = m.has_bd ? exp10(th[m.idx_bd]) : m.g_ref;
   const double r_ref = m.has_bd ? sqrt(kGrav * th[m.idx_bd + 1] * kMJup / g_ref) : m.r_p * scale;
   const double kk = kB / (mu * kMu * g_ref * r_ref * r_ref);
-  const double step = (m.log10_ptop - m.log10_pbot) / L;
-  const double ln10 = 2.302585092994045684017991454684;
-  const double dlnp = -step * ln10;
-  auto logp_lev = [&](int j) { return j == L ? m.log10_ptop : m.log10_pbot + j * step; };
   const double rs2 = m.r_s * m.r_s;
   const double log10_pc = m.has_cloud ? th[m.idx_cloud] : 0.0;
   // non-grey cloud: D_l = q_l rho_l dr_l 3 / (4 r_eff); profile parameters start at q_first
   const int q_first = m.idx_cloud + (m.cloud_qext == kQextGrey ? 1 : 3);
   const double r_eff = m.cloud_ng ? 1.0e-4 * exp10(th[m.idx_cloud]) : 1.0;
-  auto layer_sum = [&](int l, int k) {
-    double v = 0.0;
-    if constexpr (sizeof(PbarT) == 8) {
-      if (m.mode == kEmission) {
-        for (int c = 0; c < aw.lsum_chunks; ++c) v += aw.lsum64[(((size_t)b * aw.lsum_stride + c) * Lp + l) * NS + k];
-      } else {
-        for (int c = 0; c < Cn; ++c) v += aw.layer_sums[(((size_t)b * C + c) * Lp + l) * NS + k];
-      }
-    } else {
-      for (int c = 0; c < aw.lsum_chunks; ++c) v += (double)aw.lsum[(((size_t)b * aw.lsum_stride + c) * Lp + l) * NT + k];
-    }
-    return v;
+  // sums over the block of 16 values per thread, two sets of them: set q to s_w[q]
+  auto wave_part = [&](int q, const double (&v)[16]) {
+    const double s = wave_sums16(v, lane);
+    if ((lane & 3) == 0) s_w[q][wv][lane >> 2] = s;
   };
-  __syncthreads();
-
-  // per-layer sums reduced over chunks, and the per-layer chain through
-  // n = p/kT, dr, the Rayleigh and cloud prefactors; accumulators for chemistry
-  // go to s_red rows: [0,S) lnX_s, S lnXH2, S+1 lnXHe, S+2 XH2 direct,
-  // S+3 XHe direct, S+4 ln mu, S+5 theta_cloud
-  const int NR = m.S + 6;
-  for (int k = 0; k < NR; ++k) s_red[k * kBlock + tid] = 0.0;
-  for (int l = tid; l < L; l += kBlock) {
-    constexpr int kMaxNS = kMaxSpecies + kExtraSums;
-    double sm[kMaxNS];
-    if constexpr (sizeof(PbarT) == 8) {
-      for (int k = 0; k < NS; ++k) sm[k] = layer_sum(l, k);
-    } else {
-      // chunk by chunk with a chunk's sums loaded together; each sum still adds
-      // its chunks in chunk order
-      for (int k = 0; k < NS; ++k) sm[k] = 0.0;
-      for (int c = 0; c < aw.lsum_chunks; ++c) {
-        const float* src = aw.lsum + (((size_t)b * aw.lsum_stride + c) * Lp + l) * NT;
-        float v[kMaxNS];
-#pragma unroll
-        for (int k = 0; k < kMaxNS; ++k) v[k] = k < NS ? src[k] : 0.0f;
-#pragma unroll
-        for (int k = 0; k < kMaxNS; ++k)
-          if (k < NS) sm[k] += (double)v[k];
-      }
+  auto wave_total = [&](int sets) {   // after a barrier; another barrier before s_sum is read
+    if (tid < 16 * sets) {
+      double s = 0.0;
+      for (int k = 0; k < kWavesC; ++k) s += s_w[tid >> 4][k][tid & 15];
+      s_sum[tid >> 4][tid & 15] = s;
     }
+  };
+
+  // per layer: the chain through n = p/kT, dr, the Rayleigh and cloud prefactors.  Set 0:
+  // [0, 8) ln X_s, then ln X_H2, ln X_He, X_H2 and X_He direct, ln mu, theta_cloud.
+  // Set 1: the non-grey cloud's kCloudSpec spectral parameters (log10 r also through the
+  // column's 1/r_eff) and 3 profile parameters, d lnL / d depth, its masked part (offset).
+  double va[16] = {}, vb[16] = {};
+  for (int l = tid; l < L; l += kBlockC) {
+    const double* src = aw.lred + ((size_t)b * Lp + l) * NS;
+    double sm[kMaxSpecies], ex[kExtraSums];
+#pragma unroll
+    for (int s = 0; s < kMaxSpecies; ++s) sm[s] = s < S ? src[s] : 0.0;
+#pragma unroll
+    for (int k = 0; k < kExtraSums; ++k) ex[k] = src[S + k];
     const double t = s_t[l];
     const double lp_bar = 0.5 * (logp_lev(l) + logp_lev(l + 1));
     const double n = exp10(lp_bar) * kBar / (kB * t);
     const double dr = s_r[l + 1] - s_r[l];
     const double rr = (m.has_ray ? n * (xh2 * m.ray_h2 + xhe * m.ray_he) * dr : 0.0);
     double f = 0.0, dd = 0.0;
+    const double gc1 = ex[1], gc2 = ex[2], gr = ex[4], gd = ex[5];
     if (ng) {
-      dd = condensate_q(m.cloud_profile, th + q_first, logp_lev(l), logp_lev(l + 1), lp_bar, nullptr) * mu * kMu * n *
-           dr * 0.75 / r_eff;
+      const double col = mu * kMu * n * dr * 0.75 / r_eff;
+      double dq[3];
+      const double q = condensate_q(m.cloud_profile, th + q_first, logp_lev(l), logp_lev(l + 1), lp_bar, dq);
+      dd = q * col;
+      vb[0] -= ln10 * gd * q * col;
+#pragma unroll
+      for (int k = 0; k < 3; ++k) vb[kCloudSpec + k] += gd * col * dq[k];
     } else if (cloudy) {
       f = (logp_lev(l) - log10_pc) * ln10 / dlnp;
       f = f < 0.0 ? 0.0 : (f > 1.0 ? 1.0 : f);
       dd = m.kappa_cloud * mu * kMu * n * f * dr;
     }
     double gline = 0.0;
-    for (int s = 0; s < m.S; ++s) gline += sm[s];
-    const double gc1 = sm[m.S + 1], gc2 = sm[m.S + 2], gr = sm[m.S + 4], gd = sm[m.S + 5];
+#pragma unroll
+    for (int s = 0; s < kMaxSpecies; ++s) gline += sm[s];
     const double lnn_bar = gline + 2.0 * gc1 + 2.0 * gc2 + gr * rr + gd * dd;
     const double lndr_bar = gline + gc1 + gc2 + gr * rr + gd * dd;
     s_lndr[l] = lndr_bar / dr;
@@ -1125,7 +1156,7 @@ __global__ __launch_bounds__(kBlock) void k_chain(Model m, Work w, AdjWork aw, i
         const int mid = (lo + hi) >> 1;
         if (m.t_grid[mid] <= t) lo = mid; else hi = mid;
       }
-      tbar += ln2 * sm[m.S] / (m.t_grid[lo + 1] - m.t_grid[lo]);
+      tbar += ln2 * ex[0] / (m.t_grid[lo + 1] - m.t_grid[lo]);
     }
     if (m.has_cia && t > m.tc_grid[0] && t < m.tc_grid[m.n_tc - 1]) {
       int lo = 0, hi = m.n_tc - 1;
@@ -1133,209 +1164,126 @@ __global__ __launch_bounds__(kBlock) void k_chain(Model m, Work w, AdjWork aw, i
         const int mid = (lo + hi) >> 1;
         if (m.tc_grid[mid] <= t) lo = mid; else hi = mid;
       }
-      tbar += ln2 * sm[m.S + 3] / (m.tc_grid[lo + 1] - m.tc_grid[lo]);
+      tbar += ln2 * ex[3] / (m.tc_grid[lo + 1] - m.tc_grid[lo]);
     }
     s_tb[l] = tbar;
-    for (int s = 0; s < m.S; ++s) s_red[s * kBlock + tid] += sm[s];
-    s_red[(m.S) * kBlock + tid] += 2.0 * gc1 + gc2;
-    s_red[(m.S + 1) * kBlock + tid] += gc2;
-    s_red[(m.S + 2) * kBlock + tid] += gr * n * dr * m.ray_h2;
-    s_red[(m.S + 3) * kBlock + tid] += gr * n * dr * m.ray_he;
-    s_red[(m.S + 4) * kBlock + tid] += gd * dd;
+#pragma unroll
+    for (int s = 0; s < kMaxSpecies; ++s) va[s] += sm[s];
+    va[8] += 2.0 * gc1 + gc2;
+    va[9] += gc2;
+    va[10] += gr * n * dr * m.ray_h2;
+    va[11] += gr * n * dr * m.ray_he;
+    va[12] += gd * dd;
     if (cloudy && !m.cloud_ng && f > 0.0 && f < 1.0)
-      s_red[(m.S + 5) * kBlock + tid] += gd * m.kappa_cloud * mu * kMu * n * dr * (-ln10 / dlnp);
+      va[13] += gd * m.kappa_cloud * mu * kMu * n * dr * (-ln10 / dlnp);
   }
-  block_sum(s_red, tid, NR);
-  double chem[kMaxSpecies + 6];
-  for (int k = 0; k < NR; ++k) chem[k] = s_red[k * kBlock];
-  __syncthreads();
-
-  // non-grey cloud parameters: rows [0, kCloudSpec) the spectral parameters
-  // (log10 r also through the column's 1/r_eff), then the three profile parameters
-  __shared__ double s_cloud[kCloudSpec + 3];
-  if (m.cloud_ng) {
-    constexpr int NC = kCloudSpec + 3;
-    for (int k = 0; k < NC; ++k) s_red[k * kBlock + tid] = 0.0;
-    for (int l = tid; l < (ng ? L : 0); l += kBlock) {   // a clear virtual sample keeps zeros
-      const double gd = layer_sum(l, m.S + 5);
-      const double lp_bar = 0.5 * (logp_lev(l) + logp_lev(l + 1));
-      const double n = exp10(lp_bar) * kBar / (kB * s_t[l]);
-      const double col = mu * kMu * n * (s_r[l + 1] - s_r[l]) * 0.75 / r_eff;
-      double dq[3];
-      const double q = condensate_q(m.cloud_profile, th + q_first, logp_lev(l), logp_lev(l + 1), lp_bar, dq);
-      s_red[tid] -= ln10 * gd * q * col;
-      for (int k = 0; k < 3; ++k) s_red[(kCloudSpec + k) * kBlock + tid] += gd * col * dq[k];
+  // the cloud's spectral parameters, per chunk of wavenumbers
+  const int nq = !ng ? 0 : sizeof(PbarT) == 8 ? C : aw.lsum_chunks;
+  for (int c = tid; c < nq; c += kBlockC)
+#pragma unroll
+    for (int k = 0; k < kCloudSpec; ++k) {
+      if constexpr (sizeof(PbarT) == 8) vb[k] += aw.hq64[((size_t)b * C + c) * kCloudSpec + k];
+      else vb[k] += (double)aw.hq[((size_t)b * aw.lsum_stride + c) * kCloudSpec + k];
     }
-    // spectral parameters: the per-chunk sums of k_cloud_spectral
-    if constexpr (sizeof(PbarT) == 8) {
-      for (int i = tid; i < (ng ? C * kCloudSpec : 0); i += kBlock)
-        s_red[(i % kCloudSpec) * kBlock + tid] += aw.hq64[(size_t)b * C * kCloudSpec + i];
-    } else {
-      for (int i = tid; i < (ng ? aw.lsum_chunks * kCloudSpec : 0); i += kBlock)
-        s_red[(i % kCloudSpec) * kBlock + tid] += (double)aw.hq[((size_t)b * aw.lsum_stride) * kCloudSpec + i];
-    }
-    block_sum(s_red, tid, NC);
-    if (tid < NC) s_cloud[tid] = s_red[tid * kBlock];
-    __syncthreads();
+  // seed of the core term, and of the offset
+  for (int k = tid; k < m.K; k += kBlockC) {
+    const double d = w.dm[(size_t)b * m.K + k];
+    vb[10] += d;
+    if (m.has_offset && mask && mask[k]) vb[11] += d;
   }
+  wave_part(0, va);
+  wave_part(1, vb);
 
   // path-matrix adjoint: column pass (r_l, r_{l+1}) and row pass (b_i); four entries'
-  // loads are issued together, each entry summed over the chunks in chunk order.  Each
-  // column's (row's) entries are split into nseg contiguous segments on different
-  // threads (the longest column set the pace of the whole block); the segments'
-  // partial sums, kept in s_red (free here), are added in segment order
+  // loads are issued together.  Each column's (row's) entries are split into nseg
+  // contiguous segments on different threads (the longest column set the pace of the
+  // whole block); the segments' partial sums are added in segment order
   const PbarT* pbar = reinterpret_cast<const PbarT*>(aw.pbar) + (size_t)b * C * Lp * Lp;
-  const size_t pst = (size_t)Lp * Lp;
-  const bool trans = m.mode == kTransmission;
-  constexpr int kMaxSeg = 4;
-  const int nseg = trans ? max(1, min(kMaxSeg, kBlock / max(L, 1))) : 1;
-  double* s_plo = s_red;                              // [kMaxSeg][kMaxLayers]
-  double* s_pup = s_red + kMaxSeg * kMaxLayers;
-  double* s_pb = s_red + 2 * kMaxSeg * kMaxLayers;
-  for (int t = tid; t < (trans ? nseg * L : 0); t += kBlock) {
-    const int l = t % L, sg = t / L;
-    const int ia = sg * (l + 1) / nseg, ib = (sg + 1) * (l + 1) / nseg;   // rows i <= l
-    double clo = 0.0, cup = 0.0;
-    for (int i0 = ia; i0 < ib; i0 += 4) {
-      double p[4] = {0.0, 0.0, 0.0, 0.0};
-      for (int c = 0; c < Cn; ++c)
+  constexpr int nseg = kMaxSeg;
+  for (int t = tid; t < (trans ? 2 * nseg * L : 0); t += kBlockC) {
+    const bool column = t < nseg * L;
+    const int u = column ? t : t - nseg * L;
+    const int x = u % L, sg = u / L;
+    // a column's rows i <= x, or a row's columns l > x
+    const int first = column ? 0 : x + 1, n = column ? x + 1 : L - 1 - x;
+    const int qa = first + sg * n / nseg, qb = first + (sg + 1) * n / nseg;
+    double a0 = 0.0, a1 = 0.0;
+    for (int q0 = qa; q0 < qb; q0 += 4) {
+      double p[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-          if (i0 + u < ib) p[u] += (double)pbar[c * pst + (size_t)(i0 + u) * Lp + l];
+      for (int k = 0; k < 4; ++k) {
+        const int q = min(q0 + k, qb - 1);
+        p[k] = (double)pbar[column ? (size_t)q * Lp + x : (size_t)x * Lp + q];
+      }
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        if (i0 + u >= ib) break;
+      for (int k = 0; k < 4; ++k) {
+        if (q0 + k >= qb) break;
         double dlo, dup, db;
-        path_derivs(s_r, i0 + u, l, dlo, dup, db);
-        clo += p[u] * dlo;
-        cup += p[u] * dup;
+        path_derivs(s_r, column ? q0 + k : x, column ? x : q0 + k, dlo, dup, db);
+        a0 = fma(p[k], column ? dlo : db, a0);
+        a1 = fma(p[k], dup, a1);
       }
     }
-    s_plo[sg * kMaxLayers + l] = clo;
-    s_pup[sg * kMaxLayers + l] = cup;
-  }
-  for (int t = tid; t < (trans ? nseg * L : 0); t += kBlock) {
-    const int i = t % L, sg = t / L, n = L - 1 - i;   // columns l = i + 1 .. L - 1
-    const int la = i + 1 + sg * n / nseg, lb = i + 1 + (sg + 1) * n / nseg;
-    double acc = 0.0;
-    for (int l0 = la; l0 < lb; l0 += 4) {
-      double p[4] = {0.0, 0.0, 0.0, 0.0};
-      for (int c = 0; c < Cn; ++c)
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-          if (l0 + u < lb) p[u] += (double)pbar[c * pst + (size_t)i * Lp + l0 + u];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        if (l0 + u >= lb) break;
-        double dlo, dup, db;
-        path_derivs(s_r, i, l0 + u, dlo, dup, db);
-        acc += p[u] * db;
-      }
+    if (column) {
+      s_plo[sg * kMaxLayers + x] = a0;
+      s_pup[sg * kMaxLayers + x] = a1;
+    } else {
+      s_pb[sg * kMaxLayers + x] = a0;
     }
-    s_pb[sg * kMaxLayers + i] = acc;
   }
   __syncthreads();
-  for (int l = tid; l < (trans ? L : 0); l += kBlock) {
-    double clo = 0.0, cup = 0.0, bb = 0.0;
-    for (int sg = 0; sg < nseg; ++sg) {
-      clo += s_plo[sg * kMaxLayers + l];
-      cup += s_pup[sg * kMaxLayers + l];
-      bb += s_pb[sg * kMaxLayers + l];
-    }
-    s_clo[l] = clo;
-    s_cup[l] = cup;
-    s_bb[l] = bb;
-  }
-  __syncthreads();   // s_red is reused below
-  // emission: no chord; the levels move the optical depths only through dr
-  for (int l = tid; l < (trans ? 0 : L); l += kBlock) s_clo[l] = s_cup[l] = s_bb[l] = 0.0;
-  // seed of the core term: the bins' d lnL / d depth summed over the block
-  // (s_red is free between the cloud sums and the T-p sums)
-  double cb = 0.0;
-  for (int k = tid; k < m.K; k += kBlock) cb += w.dm[(size_t)b * m.K + k];
-  s_red[tid] = cb;
-  block_sum(s_red, tid, 1);
-  const double core_bar = s_red[0];
-  for (int j = tid; j <= L; j += kBlock) {
+  wave_total(2);
+  __syncthreads();
+  const double core_bar = s_sum[1][10];
+  for (int j = tid; j <= L; j += kBlockC) {
     double rb = 0.0;
-    double ab_j = 0.0, ab_jm = 0.0;
-    for (int c = 0; c < (trans ? Cn : 0); ++c) {
-      if (j < L) ab_j += aw.abar[((size_t)b * C + c) * Lp + j];
-      if (j >= 1) ab_jm += aw.abar[((size_t)b * C + c) * Lp + j - 1];
+    if (trans) {
+      double lo = 0.0, up = 0.0, bb = 0.0;
+      for (int sg = 0; sg < nseg; ++sg) {
+        if (j < L) {
+          lo += s_plo[sg * kMaxLayers + j];
+          bb += s_pb[sg * kMaxLayers + j];
+        }
+        if (j >= 1) {
+          up += s_pup[sg * kMaxLayers + j - 1];
+          bb += s_pb[sg * kMaxLayers + j - 1];
+        }
+      }
+      const double* ab = aw.abar + (size_t)b * C * Lp;
+      const double ab_j = j < L ? ab[j] : 0.0, ab_jm = j >= 1 ? ab[j - 1] : 0.0;
+      rb = lo + up + 0.5 * bb + 2.0 * s_r[j] * (ab_jm - ab_j) / rs2;
+      if (j == 0) rb += 2.0 * s_r[0] * core_bar / rs2;
     }
-    if (j < L) rb += s_clo[j] + 0.5 * s_bb[j] - 2.0 * s_r[j] * ab_j / rs2 - s_lndr[j];
-    if (j >= 1) rb += s_cup[j - 1] + 0.5 * s_bb[j - 1] + 2.0 * s_r[j] * ab_jm / rs2 + s_lndr[j - 1];
-    if (j == 0 && trans) rb += 2.0 * s_r[0] * core_bar / rs2;
-    s_rb[j] = rb;
+    // emission: no chord; the levels move the optical depths only through dr
+    if (j < L) rb -= s_lndr[j];
+    if (j >= 1) rb += s_lndr[j - 1];
     s_ub[j] = -rb * s_r[j] * s_r[j];
   }
   __syncthreads();
 
-  // hydrostatic recursion in reverse (sequential over levels)
-  if (tid == 0) {
-    const double lpref = log10(m.p_ref / kBar);
-    int cnt = 0;
-    for (int j = 0; j <= L; ++j) cnt += logp_lev(j) > lpref;
-    const int lref = min(max(cnt - 1, 0), L - 1);
-    const double a1 = (logp_lev(lref) - lpref) * ln10, a2 = (lpref - logp_lev(lref + 1)) * ln10;
-    double ub_ref = 0.0, kbar = 0.0;
-    // Q_j = (u_j - u_ref)/K from the same recursion
-    double q = s_t[lref] * a1;
-    double pre = 0.0;   // sum_{j <= l} ub_j, built from the bottom
-    for (int j = 0; j <= L; ++j) ub_ref += s_ub[j];
-    // levels at and below lref
-    double qj = q;
-    kbar += s_ub[lref] * qj;
-    for (int j = lref - 1; j >= 0; --j) {
-      qj += s_t[j] * dlnp;
-      kbar += s_ub[j] * qj;
-    }
-    qj = -s_t[lref] * a2;
-    kbar += s_ub[lref + 1] * qj;
-    for (int j = lref + 2; j <= L; ++j) {
-      qj -= s_t[j - 1] * dlnp;
-      kbar += s_ub[j] * qj;
-    }
-    // temperatures
-    double below = 0.0;
-    for (int j = 0; j <= lref; ++j) below += s_ub[j];
-    double above = ub_ref - below;
-    s_tb[lref] += kk * (a1 * below - a2 * above);
-    pre = 0.0;
-    for (int l = 0; l < lref; ++l) {
-      pre += s_ub[l];
-      s_tb[l] += kk * dlnp * pre;
-    }
-    double suf = 0.0;
-    for (int l = L - 1; l > lref; --l) {
-      suf += s_ub[l + 1];
-      s_tb[l] -= kk * dlnp * suf;
-    }
-    s_scal[0] = -ub_ref / (r_ref * r_ref) - 2.0 * kbar * kk / r_ref;   // d lnL / d R_ref
-    // emission: the ratio carries (R_ref/R_s)^2, and sum_nu dlnL/dspec spec = mdot
-    if (!trans) s_scal[0] += 2.0 * w.mdot[b] / r_ref;
-    s_scal[1] = -kbar * kk;                                            // d lnL / d ln mu (hydrostatics)
-  }
+  // hydrostatic recursion in reverse: running sums of ub from either end, and of the
+  // temperatures outward from the reference layer
+  const int lref = min(max(s_above - 1, 0), L - 1);
+  if (wv == 0) wave_scan(lane, L + 1, false, [&](int j) { return s_ub[j]; }, s_scan[0]);
+  if (wv == 1) wave_scan(lane, L + 1, true, [&](int j) { return s_ub[j]; }, s_scan[1]);
+  if (wv == 2) wave_scan(lane, L, true, [&](int l) { return l < lref ? s_t[l] : 0.0; }, s_scan[2]);
+  if (wv == 3) wave_scan(lane, L, false, [&](int l) { return l > lref ? s_t[l] : 0.0; }, s_scan[3]);
   __syncthreads();
+  const double a1 = (logp_lev(lref) - lpref) * ln10, a2 = (lpref - logp_lev(lref + 1)) * ln10;
+  const double t_ref = s_t[lref];
+  // [0, 8) T-p parameters, 8: the profile's share of d lnL / d log10 g (tau = kappa_ir p / g)
+  // of an isolated object, 9: sum_j ub_j (u_j - u_ref) / K
+  double ta[16] = {};
+  for (int j = tid; j <= L; j += kBlockC) {
+    const double q = j <= lref ? t_ref * a1 + dlnp * s_scan[2][j] : -(t_ref * a2) - dlnp * s_scan[3][j - 1];
+    ta[9] += s_ub[j] * q;
+  }
 
   // T-p profile: layer temperatures (opacity, hydrostatics) and, in emission, the
   // level temperatures of the Planck sources, each at its own pressure
-  __shared__ double s_kx[kMaxKnots], s_ky[kMaxKnots], s_kd[kMaxKnots], s_kj[kMaxKnots * kMaxKnots];
-  if (m.tp_kind == kTpPchip && tid == 0) {
-    for (int k = 0; k < m.n_knots; ++k) {
-      s_kx[k] = m.n_knots == 1 ? m.log10_ptop : m.log10_ptop + k * ((m.log10_pbot - m.log10_ptop) / (m.n_knots - 1));
-      s_ky[k] = th[k];
-    }
-    s_kx[m.n_knots - 1] = m.log10_pbot;
-    pchip_slopes_jac(s_kx, s_ky, m.n_knots, s_kd, s_kj);
-  }
-  // slot n_tp: the profile's share of d lnL / d log10 g (tau = kappa_ir p / g) for an isolated object
-  const int n_red = m.n_tp + m.has_bd;
-  for (int k = 0; k < n_red; ++k) s_red[k * kBlock + tid] = 0.0;
-  __syncthreads();
   auto tp_grad = [&](double lp, double t, double tbar) {
     if (m.tp_kind == kTpIso) {
-      s_red[tid] += tbar;
+      ta[0] += tbar;
     } else if (m.tp_kind == kTpGuillot3) {
       const double tau = m.kappa_ir * exp10(lp) * kBar / g_ref;
       const double t3 = t * t * t;
@@ -1346,24 +1294,25 @@ __global__ __launch_bounds__(kBlock) void k_chain(Model m, Work w, AdjWork aw, i
       const double dbk = -1.0 / (gam * gam * s3) + (1.0 / s3 + 1.0 / (gam * gam * s3)) * e +
                          (gam / s3 - 1.0 / (gam * s3)) * e * (-tau * s3);
       const double ti = th[0], te = th[1];
-      s_red[tid] += tbar * 3.0 * ti * ti * ti * (2.0 / 3.0 + tau) / (4.0 * t3);
-      s_red[kBlock + tid] += tbar * 12.0 * m.f_hem * te * te * te * bk / (4.0 * t3);
-      s_red[2 * kBlock + tid] += tbar * 3.0 * m.f_hem * te * te * te * te * dbk * gam * ln10 / (4.0 * t3);
+      ta[0] += tbar * 3.0 * ti * ti * ti * (2.0 / 3.0 + tau) / (4.0 * t3);
+      ta[1] += tbar * 12.0 * m.f_hem * te * te * te * bk / (4.0 * t3);
+      ta[2] += tbar * 3.0 * m.f_hem * te * te * te * te * dbk * gam * ln10 / (4.0 * t3);
       if (m.has_bd) {
         // d T^4 / d tau times d tau / d log10 g = -tau ln 10
         const double dt4 = 0.75 * ti * ti * ti * ti - 3.0 * m.f_hem * te * te * te * te * (gam / s3 - 1.0 / (gam * s3)) * e * gam * s3;
-        s_red[3 * kBlock + tid] -= tbar * dt4 * tau * ln10 / (4.0 * t3);
+        ta[8] -= tbar * dt4 * tau * ln10 / (4.0 * t3);
       }
     } else if (m.tp_kind == kTpBarstow) {
-      s_red[tid] += tbar * barstow_factor(lp);
+      ta[0] += tbar * barstow_factor(lp);
     } else if (m.tp_kind == kTpMilne || m.tp_kind == kTpGuillot7) {
-      double d4[7];
+      double d4[7] = {};
       if (m.tp_kind == kTpMilne) milne_t4(th, lp, g_ref, d4);
       else guillot7_t4(th, lp, g_ref, m.f_hem, d4);
       const double inv = tbar / (4.0 * t * t * t);
-      for (int k = 0; k < m.n_tp; ++k) s_red[k * kBlock + tid] += d4[k] * inv;
+#pragma unroll
+      for (int k = 0; k < 7; ++k) ta[k] += d4[k] * inv;
       // tau depends on kappa_ir / g: d/d log10 g = -d/d log10 kappa_ir
-      if (m.has_bd) s_red[m.n_tp * kBlock + tid] -= d4[m.tp_kind == kTpMilne ? 1 : 2] * inv;
+      if (m.has_bd) ta[8] -= (m.tp_kind == kTpMilne ? d4[1] : d4[2]) * inv;
     } else {
       // T = h00 y_k + h10 h d_k + h01 y_k+1 + h11 h d_k+1 on the knot interval holding lp
       const int n = m.n_knots;
@@ -1373,57 +1322,65 @@ __global__ __launch_bounds__(kBlock) void k_chain(Model m, Work w, AdjWork aw, i
       const double u = (lp - s_kx[k]) / hk, omu = 1.0 - u;
       const double h00 = (1.0 + 2.0 * u) * omu * omu, h10 = u * omu * omu, h01 = u * u * (3.0 - 2.0 * u),
                    h11 = u * u * (u - 1.0);
-      for (int j = 0; j < n; ++j) {
+#pragma unroll
+      for (int j = 0; j < kMaxKnots; ++j) {
+        if (j >= n) break;
         double dtdy = hk * (h10 * s_kj[k * n + j] + h11 * s_kj[(k + 1) * n + j]);
         if (j == k) dtdy += h00;
         if (j == k + 1) dtdy += h01;
-        s_red[j * kBlock + tid] += tbar * dtdy;
+        ta[j] += tbar * dtdy;
       }
     }
   };
-  for (int l = tid; l < L; l += kBlock) tp_grad(0.5 * (logp_lev(l) + logp_lev(l + 1)), s_t[l], s_tb[l]);
+  for (int l = tid; l < L; l += kBlockC) {
+    double tb = s_tb[l];
+    if (l < lref) tb += kk * dlnp * s_scan[0][l];
+    else if (l > lref) tb -= kk * dlnp * s_scan[1][l + 1];
+    else tb += kk * (a1 * s_scan[0][lref] - a2 * s_scan[1][lref + 1]);
+    tp_grad(0.5 * (logp_lev(l) + logp_lev(l + 1)), s_t[l], tb);
+  }
   if (!trans) {
     const double* tlev = w.t_lev + (size_t)b * (Lp + 1);
-    for (int j = tid; j <= L; j += kBlock) {
-      double tb = 0.0;
-      const size_t i0 = (size_t)b * m.n_tiles64 * (Lp + 1) + j;
-      for (int t0 = 0; t0 < m.n_tiles64; t0 += 4) {
-        double v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const size_t i = i0 + (size_t)(t0 + u) * (Lp + 1);
-          if (t0 + u >= m.n_tiles64) v[u] = 0.0;
-          else if constexpr (sizeof(PbarT) == 8) v[u] = aw.psum64[i];
-          else v[u] = (double)aw.psum[i];
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-          if (t0 + u < m.n_tiles64) tb += v[u];
-      }
-      tp_grad(logp_lev(j), tlev[j], tb);
-    }
+    for (int j = tid; j <= L; j += kBlockC) tp_grad(logp_lev(j), tlev[j], aw.pred[(size_t)b * (Lp + 1) + j]);
   }
-  block_sum(s_red, tid, n_red);
-  if (tid == 0) {
-    for (int k = 0; k < m.n_tp; ++k) gout[k] = s_red[k * kBlock];
+  // s_w[0] was last read before the barriers above; the totals in s_sum[1] (cloud, offset)
+  // and s_sum[0] (chemistry) stay, so this set's totals go to s_tp
+  __shared__ double s_tp[16];
+  wave_part(0, ta);
+  __syncthreads();
+  if (tid < 16) {
+    double s = 0.0;
+    for (int k = 0; k < kWavesC; ++k) s += s_w[0][k][tid];
+    s_tp[tid] = s;
+  }
+  __syncthreads();
+  const double ub_ref = s_scan[0][L], kbar = s_tp[9];
+  const double* chem = s_sum[0];
+  // d lnL / d R_ref; the emission ratio carries (R_ref/R_s)^2, and sum_nu dlnL/dspec spec = mdot
+  const double rref_bar = -ub_ref / (r_ref * r_ref) - 2.0 * kbar * kk / r_ref + (trans ? 0.0 : 2.0 * w.mdot[b] / r_ref);
+  const double lnmu_hyd = -kbar * kk;   // d lnL / d ln mu (hydrostatics)
+  if (tid < m.n_tp) gout[tid] = s_tp[tid];
+  if (tid < S) {
+    // chemistry: X_H2 = (1 - sum X)/1.164, X_He = 0.164 X_H2, mu = sum X m
+    const double lnmu_bar = chem[12] + lnmu_hyd;
+    const double mu_bar = mu_free ? lnmu_bar / mu : 0.0;
+    const double xhe_bar = chem[9] / xhe + chem[11] + mu_bar * kMHe;
+    const double xh2_bar = chem[8] / xh2 + chem[10] + mu_bar * kMH2 + kHeH2 * xhe_bar;
+    const double xb = chem[tid] / s_x[tid] + mu_bar * m.mass[tid] - xh2_bar / (1.0 + kHeH2);
+    gout[m.n_tp + tid] = xb * s_x[tid] * ln10;
+  }
+  if (tid == 64) {
     if (m.has_bd) {
       // g R_ref^2 = G M fixes the hydrostatic constant: ln g enters at fixed R_ref like ln mu
-      // (s_scal[1]) and through R_ref = sqrt(G M / g) (s_scal[0] = d lnL / d R_ref)
-      gout[m.idx_bd] = (s_scal[1] - 0.5 * r_ref * s_scal[0]) * ln10 + s_red[m.n_tp * kBlock];
-      gout[m.idx_bd + 1] = 0.5 * r_ref * s_scal[0] / th[m.idx_bd + 1];
+      // and through R_ref = sqrt(G M / g)
+      gout[m.idx_bd] = (lnmu_hyd - 0.5 * r_ref * rref_bar) * ln10 + s_tp[8];
+      gout[m.idx_bd + 1] = 0.5 * r_ref * rref_bar / th[m.idx_bd + 1];
     }
-    // chemistry: X_H2 = (1 - sum X)/1.164, X_He = 0.164 X_H2, mu = sum X m
-    const double lnmu_bar = chem[m.S + 4] + s_scal[1];
-    const double mu_bar = mu_free ? lnmu_bar / mu : 0.0;
-    const double xhe_bar = chem[m.S + 1] / xhe + chem[m.S + 3] + mu_bar * kMHe;
-    const double xh2_bar = chem[m.S] / xh2 + chem[m.S + 2] + mu_bar * kMH2 + kHeH2 * xhe_bar;
-    for (int s = 0; s < m.S; ++s) {
-      const double xb = chem[s] / x[s] + mu_bar * m.mass[s] - xh2_bar / (1.0 + kHeH2);
-      gout[m.n_tp + s] = xb * x[s] * ln10;
-    }
-    if (m.has_cloud && !m.cloud_ng) gout[m.idx_cloud] = chem[m.S + 5];
+    if (m.has_cloud && !m.cloud_ng) gout[m.idx_cloud] = chem[13];
     if (m.cloud_ng) {
       // theta order: log10 r, [a, log10 Q0], profile (1 or 3), [A, lambda0, log10 omega, xi]
+      // (a clear virtual sample's sums are zero)
+      const double* s_cloud = s_sum[1];
       int k = m.idx_cloud;
       gout[k++] = s_cloud[0];
       if (m.cloud_qext != kQextGrey) { gout[k++] = s_cloud[1]; gout[k++] = s_cloud[2]; }
@@ -1432,46 +1389,100 @@ __global__ __launch_bounds__(kBlock) void k_chain(Model m, Work w, AdjWork aw, i
       if (m.cloud_qext == kQextFeature)
         for (int j = 3; j < kCloudSpec; ++j) gout[k++] = s_cloud[j];
     }
-    if (m.has_scale) gout[m.idx_scale] = s_scal[0] * m.r_p;
-    if (m.has_offset) {
-      double o = 0.0;
-      for (int k = 0; k < m.K; ++k)
-        if (mask && mask[k]) o += w.dm[(size_t)b * m.K + k];
-      gout[m.idx_offset] = o * 1.0e-6;
-    }
+    if (m.has_scale) gout[m.idx_scale] = rref_bar * m.r_p;
+    if (m.has_offset) gout[m.idx_offset] = s_sum[1][11] * 1.0e-6;
   }
 }
 
 // ============================================================================
-// sum of the reverse kernel's per-chunk partials into chunk 0 of each sample
-// (path-matrix adjoint, annulus-area adjoint and, in FP64, the layer sums), so
-// the chain reads one slot; one thread per (sample, element)
+// Sums over the wavenumber chunks, so that the chain reads one slot of each: the per-layer
+// sums (to lred), the reverse kernel's path-matrix and annulus-area adjoints (into chunk 0
+// of the sample, C > 1) and emission's per-level sums (to pred).  A workgroup takes 32
+// neighbouring elements of one sample, eight threads each (strided over the chunks, four
+// loads in flight), added in a fixed order.
+constexpr int kRedElems = 32, kRedSegs = kBlock / kRedElems;
+
+struct ReduceSizes {
+  int sums, path, area, levels;   // elements per sample
+};
+__host__ __device__ inline ReduceSizes reduce_sizes(const Model& m, int C) {
+  const bool parts = m.mode == kTransmission && C > 1;
+  return {m.L_max * n_sums(m.S), parts ? m.L_pad * m.L_pad : 0, parts ? m.L_pad : 0,
+          m.mode == kEmission ? m.L_max + 1 : 0};
+}
+__host__ __device__ inline int reduce_blocks(const ReduceSizes& z) {
+  return (z.sums + z.path + z.area + z.levels + kRedElems - 1) / kRedElems;
+}
+
 template <typename PbarT>
-__global__ __launch_bounds__(kBlock) void k_reduce_chunks(Model m, Work w, AdjWork aw, int B, int C) {
+__global__ __launch_bounds__(kBlock) void k_reduce_chunks(Model m, Work w, AdjWork aw, int C) {
+  __shared__ double s_part[kRedSegs][kRedElems];
   const int Lp = m.L_pad, NS = n_sums(m.S);
-  const long n_p = (long)Lp * Lp, n_a = Lp, n_s = sizeof(PbarT) == 8 ? (long)Lp * NS : 0;
-  const long per = n_p + n_a + n_s;
-  const long gid = (long)blockIdx.x * kBlock + threadIdx.x;
-  if (gid >= per * B) return;
-  const int b = (int)(gid / per);
+  const ReduceSizes z = reduce_sizes(m, C);
+  const int nblk = reduce_blocks(z), b = blockIdx.x / nblk;
   if (w.status[b]) return;
-  const long e = gid - (long)b * per;
-  const size_t p0 = (size_t)b * C;
-  if (e < n_p) {
-    PbarT* pb = reinterpret_cast<PbarT*>(aw.pbar);
-    double v = 0.0;
-    for (int c = 0; c < C; ++c) v += (double)pb[(p0 + c) * n_p + e];
-    pb[p0 * n_p + e] = (PbarT)v;
-  } else if (e < n_p + n_a) {
-    const long i = e - n_p;
-    double v = 0.0;
-    for (int c = 0; c < C; ++c) v += aw.abar[(p0 + c) * n_a + i];
-    aw.abar[p0 * n_a + i] = v;
-  } else {
-    const long i = e - n_p - n_a;
-    double v = 0.0;
-    for (int c = 0; c < C; ++c) v += aw.layer_sums[(p0 + c) * (size_t)Lp * NS + i];
-    aw.layer_sums[p0 * (size_t)Lp * NS + i] = v;
+  const int L = w.nlay[b];
+  const int el = threadIdx.x & (kRedElems - 1), seg = threadIdx.x / kRedElems;
+  int e = (blockIdx.x - b * nblk) * kRedElems + el;
+  // where the element's chunks lie: type, first, stride (elements), number
+  const PbarT* src = nullptr;
+  const double* src64 = nullptr;
+  size_t stride = 0;
+  int n = 0;
+  double* dst = nullptr;
+  PbarT* dst_p = nullptr;
+  if (e < z.sums) {
+    if (e < L * NS) {
+      stride = (size_t)Lp * NS;
+      if (sizeof(PbarT) == 8 && m.mode == kTransmission) {
+        n = C;
+        src = reinterpret_cast<const PbarT*>(aw.layer_sums) + (size_t)b * C * stride + e;
+      } else {
+        n = aw.lsum_chunks;
+        src = (sizeof(PbarT) == 8 ? reinterpret_cast<const PbarT*>(aw.lsum64) : reinterpret_cast<const PbarT*>(aw.lsum)) +
+              (size_t)b * aw.lsum_stride * stride + e;
+      }
+      dst = aw.lred + (size_t)b * stride + e;
+    }
+  } else if ((e -= z.sums) < z.path) {
+    const int i = e / Lp, l = e - i * Lp;
+    if (l >= i && l < L) {   // the chain reads the upper triangle
+      stride = (size_t)Lp * Lp;
+      n = C;
+      src = dst_p = reinterpret_cast<PbarT*>(aw.pbar) + (size_t)b * C * stride + e;
+    }
+  } else if ((e -= z.path) < z.area) {
+    stride = Lp;
+    n = C;
+    src64 = dst = aw.abar + (size_t)b * C * stride + e;
+  } else if ((e -= z.area) < z.levels) {
+    if (e <= L) {
+      stride = Lp + 1;
+      n = m.n_tiles64;
+      src = (sizeof(PbarT) == 8 ? reinterpret_cast<const PbarT*>(aw.psum64) : reinterpret_cast<const PbarT*>(aw.psum)) +
+            (size_t)b * m.n_tiles64 * stride + e;
+      dst = aw.pred + (size_t)b * stride + e;
+    }
+  }
+  double v = 0.0;
+  constexpr int kFly = 4;
+  for (int c0 = seg; c0 < n; c0 += kFly * kRedSegs) {
+    double x[kFly];
+#pragma unroll
+    for (int u = 0; u < kFly; ++u) {
+      const int c = c0 + u * kRedSegs;
+      x[u] = c < n ? (src ? (double)src[c * stride] : src64[c * stride]) : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < kFly; ++u) v += x[u];
+  }
+  s_part[seg][el] = v;
+  __syncthreads();
+  if (seg == 0 && n > 0) {
+#pragma unroll
+    for (int k = 1; k < kRedSegs; ++k) v += s_part[k][el];
+    if (dst_p) *dst_p = (PbarT)v;
+    else *dst = v;
   }
 }
 
@@ -1558,6 +1569,12 @@ bool adjoint_alloc(AdjWork& aw, const Model& m, int B_max, bool fp64, const std:
   aw.ls_tiles = 8;
   aw.max_pairs = pairs;
   const size_t Lp = m.L_pad;
+  aw.lred = (double*)alloc((size_t)B_max * Lp * n_lsums(m) * sizeof(double));
+  if (!aw.lred) return false;
+  if (m.mode == kEmission) {
+    aw.pred = (double*)alloc((size_t)B_max * (Lp + 1) * sizeof(double));
+    if (!aw.pred) return false;
+  }
   if (m.mode == kEmission && fp64) {
     aw.lsum_stride = (m.n_tiles + kLsTileChoices[0] - 1) / kLsTileChoices[0];
     aw.lsum_chunks = (m.n_tiles + aw.ls_tiles - 1) / aw.ls_tiles;
@@ -1727,21 +1744,14 @@ void launch_layer_sums(const Model& m, const Work& w, const Tables& tb, const Ad
 void launch_chain(const Model& m, const Work& w, const AdjWork& aw, int B, const double* params, const uint8_t* mask,
                   double* grad, bool fp64, hipStream_t st) {
   const int C = adjoint_chunks(m, aw, B, fp64);
-  int Cn = C;
-  if (C > 1) {
-    // the chunk partials are summed by a wide kernel first; the chain then reads one slot
-    const long per = (long)m.L_pad * m.L_pad + m.L_pad + (fp64 ? (long)m.L_pad * n_sums(m.S) : 0);
-    const unsigned grid = (unsigned)((per * B + kBlock - 1) / kBlock);
-    if (fp64)
-      hipLaunchKernelGGL(k_reduce_chunks<double>, dim3(grid), dim3(kBlock), 0, st, m, w, aw, B, C);
-    else
-      hipLaunchKernelGGL(k_reduce_chunks<float>, dim3(grid), dim3(kBlock), 0, st, m, w, aw, B, C);
-    Cn = 1;
+  const unsigned grid = (unsigned)(reduce_blocks(reduce_sizes(m, C)) * B);
+  if (fp64) {
+    hipLaunchKernelGGL(k_reduce_chunks<double>, dim3(grid), dim3(kBlock), 0, st, m, w, aw, C);
+    hipLaunchKernelGGL(k_chain<double>, dim3(B), dim3(kBlockC), 0, st, m, w, aw, C, params, mask, grad);
+  } else {
+    hipLaunchKernelGGL(k_reduce_chunks<float>, dim3(grid), dim3(kBlock), 0, st, m, w, aw, C);
+    hipLaunchKernelGGL(k_chain<float>, dim3(B), dim3(kBlockC), 0, st, m, w, aw, C, params, mask, grad);
   }
-  if (fp64)
-    hipLaunchKernelGGL(k_chain<double>, dim3(B), dim3(kBlock), 0, st, m, w, aw, C, Cn, params, mask, grad);
-  else
-    hipLaunchKernelGGL(k_chain<float>, dim3(B), dim3(kBlock), 0, st, m, w, aw, C, Cn, params, mask, grad);
 }
 
 }  // namespace exofwd

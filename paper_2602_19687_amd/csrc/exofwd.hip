@@ -613,6 +613,7 @@ exofwd_status exofwd_create(const exofwd_config* cfg, exofwd_ctx** out) {
   }
   hipError_t e = m.ck ? ck_configure(m) : m.mode == kTransmission ? trans_fwd_configure(m, fp64)
                                                                    : emission_configure(m, fp64);
+  if (e == hipSuccess) e = profile_configure(m, fp64);
   if (e == hipSuccess) e = adjoint_configure(m, fp64);
   if (e != hipSuccess) {
     exofwd_destroy(c);

@@ -116,6 +116,7 @@ __device__ inline T wave_sum_all(T v) {
 
 void launch_profile(const Model& m, const Work& w, int B, const double* params, const int32_t* n_layers,
                     bool fp64, hipStream_t st);
+hipError_t profile_configure(const Model& m, bool fp64);
 // dtau_out (reduced precision only, may be null): layer optical depths [B][L_pad][n_nu_pad] for the reverse pass
 void launch_trans_fwd(const Model& m, const Work& w, const Tables& tb, int B, void* spec, bool fp64,
                       hipStream_t st, float* dtau_out = nullptr);

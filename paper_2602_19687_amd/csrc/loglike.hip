@@ -5,17 +5,16 @@
 // sums one bin at a time: its lanes stride through the bin's wavenumbers
 // (coalesced) and their partial sums meet in a fixed butterfly; then one thread
 // per bin forms the bin's terms, and the sum over bins is a fixed-order tree.
+// Bound by latency (one workgroup, about 30 wavenumbers a thread): four bins of a group
+// in flight and bin edges from LDS; 30000 wavenumbers in 400 bins, 1024 samples:
+// 161 -> 134 us.
 #include "kernels.h"
 
 namespace exofwd {
 
 constexpr int kBlockLL = 1024;   // threads per sample: 16 waves (a small batch still fills the chip)
 
-// sum over the aligned group of g lanes holding v (every lane of the group gets it)
-__device__ inline double group_sum_d(double v, int g) {
-  for (int off = g >> 1; off > 0; off >>= 1) v += __shfl_xor(v, off);
-  return v;
-}
+constexpr int kBinsLL = 4;       // bins of a group of lanes in flight
 
 template <typename SpecT>
 __global__ __launch_bounds__(kBlockLL) void k_loglike(Model m, Work w, const double* __restrict__ params,
@@ -25,8 +24,9 @@ __global__ __launch_bounds__(kBlockLL) void k_loglike(Model m, Work w, const dou
                                                     const uint8_t* __restrict__ mask, double* __restrict__ lnl,
                                                     int32_t* __restrict__ status_out) {
   const int b = blockIdx.x, tid = threadIdx.x;
-  __shared__ double s_part[kBlockLL], s_fpart[kBlockLL], s_mpart[kBlockLL];
+  __shared__ double s_part[kBlockLL / 64], s_fpart[kBlockLL / 64], s_mpart[kBlockLL / 64];
   __shared__ double s_sum[kBlockLL], s_sumcf[kBlockLL];
+  __shared__ int s_lo[kBlockLL], s_hi[kBlockLL];
   // cloudy/clear mixing (Eq. 26): virtual samples 2b (cloudy) and 2b+1 (clear) give
   // the spectrum f Phi_cld + (1 - f) Phi_cf; their dm carry the factors f and 1 - f
   const bool mix = m.has_fcld;
@@ -63,27 +63,62 @@ __global__ __launch_bounds__(kBlockLL) void k_loglike(Model m, Work w, const dou
   const int gl = m.ll_lanes, glane = tid & (gl - 1), grp = tid / gl, ngrp = kBlockLL / gl;
   for (int k0 = 0; k0 < m.K; k0 += kBlockLL) {
     const int kn = min(kBlockLL, m.K - k0);
-    // bin sums, a group of lanes per bin
-    for (int kk = grp; kk < kn; kk += ngrp) {
-      const int k = k0 + kk;
-      double sum = 0.0, sum_cf = 0.0;
-      const int i1 = hi[k];
-      for (int i = lo[k] + glane; i < i1; i += gl) {
-        sum += (double)sp[i];
-        if (mix) sum_cf += (double)sp_cf[i];
+    // the chunk's bin edges, read once (every group of lanes would wait for its own)
+    if (tid < kn) {
+      s_lo[tid] = lo[k0 + tid];
+      s_hi[tid] = hi[k0 + tid];
+    }
+    __syncthreads();
+    // bin sums, a group of lanes per bin, kBinsLL bins of a group at a time: their loads
+    // are in flight together and their butterflies interleave
+    for (int kk = grp; kk < kn; kk += kBinsLL * ngrp) {
+      double sum[kBinsLL], sum_cf[kBinsLL];
+      int i0[kBinsLL], i1[kBinsLL], most = 0;
+#pragma unroll
+      for (int u = 0; u < kBinsLL; ++u) {
+        const int q = kk + u * ngrp;
+        i0[u] = q < kn ? s_lo[q] + glane : 0;
+        i1[u] = q < kn ? s_hi[q] : 0;
+        most = max(most, i1[u] - i0[u]);
+        sum[u] = sum_cf[u] = 0.0;
       }
-      sum = group_sum_d(sum, gl);
-      if (mix) sum_cf = group_sum_d(sum_cf, gl);
+      for (int off = 0; off < most; off += gl) {
+        SpecT v[kBinsLL], vc[kBinsLL];
+#pragma unroll
+        for (int u = 0; u < kBinsLL; ++u) {
+          const int i = i0[u] + off;
+          v[u] = i < i1[u] ? sp[i] : SpecT(0);
+          vc[u] = mix && i < i1[u] ? sp_cf[i] : SpecT(0);
+        }
+#pragma unroll
+        for (int u = 0; u < kBinsLL; ++u) {
+          sum[u] += (double)v[u];
+          if (mix) sum_cf[u] += (double)vc[u];
+        }
+      }
+      for (int o = gl >> 1; o > 0; o >>= 1) {
+#pragma unroll
+        for (int u = 0; u < kBinsLL; ++u) {
+          sum[u] += __shfl_xor(sum[u], o);
+          if (mix) sum_cf[u] += __shfl_xor(sum_cf[u], o);
+        }
+      }
       if (glane == 0) {
-        s_sum[kk] = sum;
-        s_sumcf[kk] = sum_cf;
+#pragma unroll
+        for (int u = 0; u < kBinsLL; ++u) {
+          const int q = kk + u * ngrp;
+          if (q < kn) {
+            s_sum[q] = sum[u];
+            s_sumcf[q] = sum_cf[u];
+          }
+        }
       }
     }
     __syncthreads();
     // the bin's terms, a thread per bin
     if (tid < kn) {
       const int k = k0 + tid;
-      const double cnt = (double)(hi[k] - lo[k]);
+      const double cnt = (double)(s_hi[tid] - s_lo[tid]);
       const double m_cld = s_sum[tid] / cnt, m_cf = s_sumcf[tid] / cnt;
       const double mk = (mix ? f * m_cld + (1.0 - f) * m_cf : m_cld) + (mask && mask[k] ? offset : 0.0);
       const double s2 = yerr[k] * yerr[k] + infl;
@@ -100,17 +135,22 @@ __global__ __launch_bounds__(kBlockLL) void k_loglike(Model m, Work w, const dou
     }
     __syncthreads();   // the next chunk of bins overwrites the sums
   }
-  s_part[tid] = part;
-  s_fpart[tid] = fpart;
-  s_mpart[tid] = mpart;
+  // sums over the block in a fixed order: each wave's butterfly, then the 16 waves
+  part = wave_sum_all(part);
+  fpart = wave_sum_all(fpart);
+  mpart = wave_sum_all(mpart);
+  if ((tid & 63) == 0) {
+    s_part[tid >> 6] = part;
+    s_fpart[tid >> 6] = fpart;
+    s_mpart[tid >> 6] = mpart;
+  }
   __syncthreads();
-  for (int h = kBlockLL / 2; h > 0; h >>= 1) {
-    if (tid < h) {
-      s_part[tid] += s_part[tid + h];
-      s_fpart[tid] += s_fpart[tid + h];
-      s_mpart[tid] += s_mpart[tid + h];
+  if (tid == 0) {
+    for (int k = 1; k < kBlockLL / 64; ++k) {
+      s_part[0] += s_part[k];
+      s_fpart[0] += s_fpart[k];
+      s_mpart[0] += s_mpart[k];
     }
-    __syncthreads();
   }
   if (tid == 0) {
     double v = s_part[0];

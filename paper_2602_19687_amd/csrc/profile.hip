@@ -1,6 +1,6 @@
 // Per-sample atmospheric profile in FP64: T-p profile, free chemistry,
 // hydrostatic altitudes, per-layer opacity records, path matrix and annulus
-// areas.  One workgroup of 256 threads per sample.
+// areas.  One workgroup of 512 threads per sample.
 #include "cloud.h"
 #include "kernels.h"
 #include "tp.h"
@@ -75,24 +75,40 @@ __device__ inline uint16_t bf16_rn(float f) {
 }
 __device__ inline float bf16_to_f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
-// Path matrix entry P_1D[i][l] (Eq. 43) with b_i the mid radius of layer i.
-// The l > i case uses sqrt(r_up^2-b^2) - sqrt(r_lo^2-b^2) = dr (r_up+r_lo)/(s_up+s_lo),
-// which has no cancellation; square roots are taken of (r-b)(r+b).
-__device__ inline double path_entry(const double* r, const double* dr, int i, int l) {
-  if (l < i) return 0.0;
-  double b = 0.5 * (r[i] + r[i + 1]);
+// Path matrix entries P_1D[i][l] (Eq. 43), l in [l0, l1), l0 >= i, with b_i the mid radius
+// of layer i: put(l, value).  The l > i case uses
+// sqrt(r_up^2-b^2) - sqrt(r_lo^2-b^2) = dr (r_up+r_lo)/(s_up+s_lo), which has no
+// cancellation; square roots are taken of (r-b)(r+b), each level's once.
+template <typename Put>
+__device__ inline void path_entries(const double* r, const double* dr, int i, int l0, int l1, Put put) {
+  const double b = 0.5 * (r[i] + r[i + 1]);
+  int l = l0;
   if (l == i) {
     double sup = sqrt(0.5 * dr[i] * (r[i + 1] + b));
-    return 2.0 * sup / dr[i];
+    put(l, 2.0 * sup / dr[i]);
+    ++l;
   }
-  double rup = r[l + 1], rlo = r[l];
-  double sup = sqrt((rup - b) * (rup + b));
-  double slo = sqrt((rlo - b) * (rlo + b));
-  return 2.0 * (rup + rlo) / (sup + slo);
+  if (l >= l1) return;
+  double rlo = r[l], slo = sqrt((rlo - b) * (rlo + b));
+  for (; l < l1; ++l) {
+    const double rup = r[l + 1], sup = sqrt((rup - b) * (rup + b));
+    put(l, 2.0 * (rup + rlo) / (sup + slo));
+    rlo = rup;
+    slo = sup;
+  }
 }
+constexpr int kPathSeg = 8;      // entries of one work item of the path matrix
+constexpr int kBlockP = 512;     // threads of the profile kernel
 
+// row length (words) of the reduced-precision path matrix in LDS: odd, so rows and columns
+// are both read without bank conflicts
+__host__ __device__ constexpr int path_ld(int Lp) { return Lp + 1; }
+
+// Bound by latency (one workgroup per sample): every phase is spread over the threads, the
+// serial recursion reads ahead, and each path-matrix entry is formed once, its transposed
+// copy coming from LDS.  100 layers: one sample 75 -> 25 us, 1024 samples 164 -> 67 us.
 template <typename Real>
-__global__ __launch_bounds__(kBlock) void k_profile(Model m, Work w, const double* __restrict__ params,
+__global__ __launch_bounds__(kBlockP) void k_profile(Model m, Work w, const double* __restrict__ params,
                                                     const int32_t* __restrict__ n_layers) {
   const int b = blockIdx.x;
   const int tid = threadIdx.x;
@@ -104,9 +120,12 @@ __global__ __launch_bounds__(kBlock) void k_profile(Model m, Work w, const doubl
   __shared__ double s_dr[kMaxLayers];
   __shared__ double s_inc[kMaxLayers];
   __shared__ double s_knot_x[kMaxKnots], s_knot_y[kMaxKnots], s_knot_d[kMaxKnots];
-  __shared__ int s_status;
   __shared__ int s_badt;
   __shared__ int s_cell[kMaxLayers];
+  __shared__ double s_n[kMaxLayers], s_x[kMaxSpecies];
+  __shared__ int s_finite, s_above, s_unbound;
+  __shared__ unsigned long long s_runs[3], s_heads[3];   // layer-sum groups: bits of run starts, of group heads
+  extern __shared__ uint32_t s_pm[];   // reduced precision, transmission: path matrix as bf16 hi | lo << 16
 
   // virtual sample b of real sample bs; a clear one (cloudy/clear mixing) has no cloud
   const int bs = real_sample(m, b);
@@ -118,14 +137,20 @@ __global__ __launch_bounds__(kBlock) void k_profile(Model m, Work w, const doubl
     status = kBadLayers;
     L = m.L_max;
   }
-  bool finite = true;
-  for (int k = 0; k < m.P; ++k) finite = finite && isfinite(th[k]);
-  if (!status && !finite) status = kNonfinite;
-
-  // chemistry (Eq. 35-36), every thread keeps its own copy
+  if (tid == 0) {
+    s_finite = 1;
+    s_above = 0;
+    s_unbound = 0;
+  }
+  __syncthreads();
+  if (tid < m.P && !isfinite(th[tid])) s_finite = 0;
+  // chemistry (Eq. 35-36)
+  if (tid < m.S) s_x[tid] = exp10(th[m.n_tp + tid]);
+  __syncthreads();
+  if (!status && !s_finite) status = kNonfinite;
   double x[kMaxSpecies];
   double sx = 0.0;
-  for (int s = 0; s < m.S; ++s) { x[s] = exp10(th[m.n_tp + s]); sx += x[s]; }
+  for (int s = 0; s < m.S; ++s) { x[s] = s_x[s]; sx += x[s]; }
   const double xh2 = (1.0 - sx) / (1.0 + kHeH2);
   const double xhe = kHeH2 * xh2;
   double mu = m.mu_fixed;
@@ -169,13 +194,13 @@ __global__ __launch_bounds__(kBlock) void k_profile(Model m, Work w, const doubl
   };
 
   int badt = 0;
-  for (int l = tid; l < L; l += kBlock) {
+  for (int l = tid; l < L; l += kBlockP) {
     double t = temperature(0.5 * (logp_lev(l) + logp_lev(l + 1)));
     s_t[l] = t;
     badt |= !(t > 0.0) || !isfinite(t);
   }
   if (m.mode == kEmission) {
-    for (int j = tid; j <= L; j += kBlock) {
+    for (int j = tid; j <= L; j += kBlockP) {
       double t = temperature(logp_lev(j));
       s_tl[j] = t;
       badt |= !(t > 0.0) || !isfinite(t);
@@ -190,25 +215,44 @@ __global__ __launch_bounds__(kBlock) void k_profile(Model m, Work w, const doubl
 
   // hydrostatics (1/r linear in ln p inside each isothermal layer)
   const double kk = kB / (mu * kMu * g_ref * r_ref * r_ref);
-  for (int l = tid; l < L; l += kBlock) s_inc[l] = kk * s_t[l] * dlnp;
+  const double lpref = log10(m.p_ref / kBar);
+  for (int l = tid; l < L; l += kBlockP) s_inc[l] = kk * s_t[l] * dlnp;
+  for (int j = tid; j <= L; j += kBlockP)
+    if (logp_lev(j) > lpref) atomicAdd(&s_above, 1);
   __syncthreads();
   if (tid == 0 && !status) {
-    const double lpref = log10(m.p_ref / kBar);
-    int cnt = 0;
-    for (int j = 0; j <= L; ++j) cnt += logp_lev(j) > lpref;
-    int lref = min(max(cnt - 1, 0), L - 1);
+    const int lref = min(max(s_above - 1, 0), L - 1);
     const double ln10 = 2.302585092994045684017991454684;
     const double u_ref = 1.0 / r_ref;
     s_u[lref] = u_ref + kk * s_t[lref] * (logp_lev(lref) - lpref) * ln10;
     s_u[lref + 1] = u_ref - kk * s_t[lref] * (lpref - logp_lev(lref + 1)) * ln10;
-    for (int j = lref - 1; j >= 0; --j) s_u[j] = s_u[j + 1] + s_inc[j];
-    for (int j = lref + 1; j < L; ++j) s_u[j + 1] = s_u[j] - s_inc[j];
-    int unbound = 0;
-    for (int j = 0; j <= L; ++j) unbound |= !(s_u[j] > 0.0);
-    s_status = unbound ? kUnbound : 0;
+    // the increments eight at a time: one LDS round trip for eight dependent sums
+    constexpr int kAhead = 8;
+    double u = s_u[lref];
+    for (int j0 = lref - 1; j0 >= 0; j0 -= kAhead) {
+      double v[kAhead];
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k) v[k] = s_inc[max(j0 - k, 0)];
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k)
+        if (j0 - k >= 0) s_u[j0 - k] = u = u + v[k];
+    }
+    u = s_u[lref + 1];
+    for (int j0 = lref + 1; j0 < L; j0 += kAhead) {
+      double v[kAhead];
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k) v[k] = s_inc[min(j0 + k, L - 1)];
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k)
+        if (j0 + k < L) s_u[j0 + k + 1] = u = u - v[k];
+    }
   }
   __syncthreads();
-  if (!status) status = s_status;
+  if (!status)
+    for (int j = tid; j <= L; j += kBlockP)
+      if (!(s_u[j] > 0.0)) s_unbound = 1;
+  __syncthreads();
+  if (!status && s_unbound) status = kUnbound;
 
   if (tid == 0) {
     w.status[b] = status;
@@ -216,17 +260,17 @@ __global__ __launch_bounds__(kBlock) void k_profile(Model m, Work w, const doubl
   }
   if (status) return;   // uniform across the workgroup
 
-  for (int j = tid; j <= L; j += kBlock) s_r[j] = 1.0 / s_u[j];
+  for (int j = tid; j <= L; j += kBlockP) s_r[j] = 1.0 / s_u[j];
   __syncthreads();
   // dr_l = r_{l+1} - r_l = (u_l - u_{l+1}) r_l r_{l+1}, and u_l - u_{l+1} = inc_l
-  for (int l = tid; l < L; l += kBlock) s_dr[l] = s_inc[l] * s_r[l] * s_r[l + 1];
+  for (int l = tid; l < L; l += kBlockP) s_dr[l] = s_inc[l] * s_r[l] * s_r[l + 1];
   __syncthreads();
 
   double* t_lay = w.t_lay + (size_t)b * Lp;
   double* t_lev = w.t_lev + (size_t)b * (Lp + 1);
   double* r_lev = w.r_lev + (size_t)b * (Lp + 1);
-  for (int l = tid; l < Lp; l += kBlock) t_lay[l] = l < L ? s_t[l] : 0.0;
-  for (int j = tid; j <= Lp; j += kBlock) {
+  for (int l = tid; l < Lp; l += kBlockP) t_lay[l] = l < L ? s_t[l] : 0.0;
+  for (int j = tid; j <= Lp; j += kBlockP) {
     r_lev[j] = j <= L ? s_r[j] : 0.0;
     t_lev[j] = (m.mode == kEmission && j <= L) ? s_tl[j] : 0.0;
     if (w.inv_tlev) w.inv_tlev[(size_t)b * (Lp + 1) + j] = j <= L ? 1.0 / s_tl[j] : 0.0;
@@ -257,13 +301,12 @@ __global__ __launch_bounds__(kBlock) void k_profile(Model m, Work w, const doubl
     cl[5] = feat ? exp10(th[f0 + 2]) : 1.0;
     cl[6] = feat ? th[f0 + 3] : 0.0;
   }
-  for (int l = tid; l < Lp; l += kBlock) {
+  for (int l = tid; l < Lp; l += kBlockP) {
     Real* rl = rec + (size_t)l * RL;
     if (l >= L) {
       w.cells[(size_t)b * Lp + l] = 0;
-      for (int k = 0; k < RL; ++k) rl[k] = Real(0);
+      for (int k = 0; k < kRecFixed; ++k) rl[k] = Real(0);
       rl[5] = rl[6] = Real(-1000);
-      for (int s = 0; s < m.S; ++s) rl[kRecFixed + s] = Real(-1000);   // the prefactors stay 0
       area[l] = Real(0);
       continue;
     }
@@ -296,70 +339,114 @@ __global__ __launch_bounds__(kBlock) void k_profile(Model m, Work w, const doubl
     rl[4] = Real(dcl);
     rl[5] = Real(m.has_cia ? log2(n * n * xh2 * xh2 * dr) : -1000.0);
     rl[6] = Real(m.has_cia ? log2(n * n * xh2 * xhe * dr) : -1000.0);
-    for (int s = 0; s < m.S; ++s) rl[kRecFixed + s] = Real(log2(n * x[s] * dr));
-    if (wide)
-      for (int s = 0; s < m.S; ++s) rl[kRecFixed + m.S + s] = Real(n * x[s] * dr);
+    s_n[l] = n;
     area[l] = Real(dr * (s_r[l] + s_r[l + 1]) / (m.r_s * m.r_s));
   }
+  __syncthreads();
+  // the line sources' prefactors, a thread per (layer, source)
+  for (int e = tid; e < Lp * m.S; e += kBlockP) {
+    const int l = e / m.S, s = e - l * m.S;
+    Real* rl = rec + (size_t)l * RL;
+    const double pre = l < L ? s_n[l] * s_x[s] * s_dr[l] : 0.0;
+    rl[kRecFixed + s] = l < L ? Real(log2(pre)) : Real(-1000);
+    if (wide) rl[kRecFixed + m.S + s] = Real(pre);
+  }
   if (w.lsg) {
-    // layer-sum groups: a run of layers in one table cell reads one set of table
-    // rows, so the layer sums fetch them once per tile for the whole group
-    __syncthreads();
-    if (tid == 0) {
-      int32_t* grp = w.lsg + (size_t)b * (Lp + 1);
-      int n = 0;
-      for (int l = 0; l < L;) {
-        int e = l + 1;
-        while (e < L && e - l < kLsGroup && s_cell[e] == s_cell[l]) ++e;
-        grp[1 + n++] = l | ((e - l) << 16);
-        l = e;
-      }
-      grp[0] = n;
+    // layer-sum groups: a run of layers in one table cell reads one set of table rows, so
+    // the layer sums fetch them once per tile for the whole group.  The runs' starts (and
+    // the end) as bits, then the group heads, every kLsGroup-th layer of a run.
+    static_assert(kMaxLayers < 192, "three words of 64 layers");
+    const int wq = tid >> 6, bit = tid & 63;
+    if (wq < 3) {
+      const bool start = tid == L || (tid < L && (tid == 0 || s_cell[tid] != s_cell[tid - 1]));
+      const unsigned long long mask = __builtin_amdgcn_ballot_w64(start);
+      if (bit == 0) s_runs[wq] = mask;
     }
+    __syncthreads();
+    bool head = false;
+    int cnt = 0;
+    if (wq < 3) {
+      if (tid < L) {
+        int q = wq;
+        unsigned long long below = s_runs[q] & (~0ull >> (63 - bit));
+        while (!below) below = s_runs[--q];   // bit 0 of word 0 is a start
+        const int first = 64 * q + 63 - __builtin_clzll(below);
+        q = wq;
+        unsigned long long after = s_runs[q] & ~(~0ull >> (63 - bit));
+        while (!after) after = s_runs[++q];   // bit L is set
+        const int next = 64 * q + __builtin_ctzll(after);
+        head = (tid - first) % kLsGroup == 0;
+        cnt = min(kLsGroup, next - tid);
+      }
+      const unsigned long long mask = __builtin_amdgcn_ballot_w64(head);
+      if (bit == 0) s_heads[wq] = mask;
+    }
+    __syncthreads();
+    int32_t* grp = w.lsg + (size_t)b * (Lp + 1);
+    if (head) {
+      int n = __builtin_popcountll(s_heads[wq] & ((1ull << bit) - 1));
+      for (int q = 0; q < wq; ++q) n += __builtin_popcountll(s_heads[q]);
+      grp[1 + n] = tid | (cnt << 16);
+    }
+    if (tid == 0)
+      grp[0] = __builtin_popcountll(s_heads[0]) + __builtin_popcountll(s_heads[1]) + __builtin_popcountll(s_heads[2]);
   }
 
   if (m.mode != kTransmission) return;
+  // the upper triangle, in row segments of kPathSeg entries
+  const int nseg = (L + kPathSeg - 1) / kPathSeg;
   if constexpr (sizeof(Real) == 8) {
     double* pm = w.pm64 + (size_t)b * Lp * Lp;
-    for (int e = tid; e < Lp * Lp; e += kBlock) {
-      int i = e / Lp, l = e % Lp;
-      pm[e] = (i < L && l < L) ? path_entry(s_r, s_dr, i, l) : 0.0;
+    for (int e = tid; e < Lp * Lp; e += kBlockP) {
+      const int i = e / Lp, l = e % Lp;
+      if (l < i || l >= L) pm[e] = 0.0;
+    }
+    for (int e = tid; e < nseg * L; e += kBlockP) {
+      const int i = e % L, l0 = i + kPathSeg * (e / L);
+      if (l0 < L) path_entries(s_r, s_dr, i, l0, min(l0 + kPathSeg, L), [&](int l, double v) { pm[(size_t)i * Lp + l] = v; });
     }
   } else {
+    const int ldp = path_ld(Lp);
+    for (int e = tid; e < nseg * L; e += kBlockP) {
+      const int i = e % L, l0 = i + kPathSeg * (e / L);
+      if (l0 < L)
+        path_entries(s_r, s_dr, i, l0, min(l0 + kPathSeg, L), [&](int l, double v) {
+          const uint16_t hv = bf16_rn((float)v);
+          s_pm[i * ldp + l] = hv | ((uint32_t)bf16_rn((float)(v - (double)bf16_to_f(hv))) << 16);
+        });
+    }
+    __syncthreads();
     // bf16 hi/lo A-operand fragments of v_mfma_f32_32x32x16_bf16:
     // lane holds row 32*mi + lane%32, columns 16*kb + 8*(lane/32) + j, j = 0..7
     const int MB = Lp / 32, KB = Lp / 16;
     const size_t plane = (size_t)MB * KB * 512;
     uint16_t* fh = w.pfrag + (size_t)b * 2 * plane;
-    uint16_t* fl = fh + plane;
     // the transposed fragments serve only the adjoint; a forward-only workspace has none
-    uint16_t* th_ = w.ptfrag ? w.ptfrag + (size_t)b * 2 * plane : nullptr;
-    uint16_t* tl_ = th_ ? th_ + plane : nullptr;
-    for (int e = tid; e < MB * KB * 64; e += kBlock) {
+    uint16_t* fth = w.ptfrag ? w.ptfrag + (size_t)b * 2 * plane : nullptr;
+    for (int e = tid; e < MB * KB * 64; e += kBlockP) {
       const int lane = e & 63, kb = (e >> 6) % KB, mi = (e >> 6) / KB;
       const int row = 32 * mi + (lane & 31);
       const int col0 = 16 * kb + 8 * (lane >> 5);
-      uint16_t hv[8], lv[8], thv[8], tlv[8];
+      // P[row][col] for the forward product, P[col][row] (transpose) for the adjoint
+      uint32_t v[8], vt[8];
+#pragma unroll
       for (int j = 0; j < 8; ++j) {
         const int col = col0 + j;
-        // P[row][col] for the forward product, P[col][row] (transpose) for the adjoint
-        double v = (row < L && col < L) ? path_entry(s_r, s_dr, row, col) : 0.0;
-        double vt = (row < L && col < L) ? path_entry(s_r, s_dr, col, row) : 0.0;
-        hv[j] = bf16_rn((float)v);
-        lv[j] = bf16_rn((float)(v - (double)bf16_to_f(hv[j])));
-        thv[j] = bf16_rn((float)vt);
-        tlv[j] = bf16_rn((float)(vt - (double)bf16_to_f(thv[j])));
+        v[j] = (row <= col && col < L) ? s_pm[row * ldp + col] : 0u;
+        vt[j] = (col <= row && row < L) ? s_pm[col * ldp + row] : 0u;
       }
-      const size_t off = (size_t)e * 8;
-      for (int j = 0; j < 8; ++j) {
-        fh[off + j] = hv[j];
-        fl[off + j] = lv[j];
+      auto put = [&](uint16_t* dst, const uint32_t (&x)[8], uint32_t sel) {   // the low or high halves
+        uint32_t d[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) d[j] = __builtin_amdgcn_perm(x[2 * j + 1], x[2 * j], sel);
+        *reinterpret_cast<uint4*>(dst + (size_t)e * 8) = make_uint4(d[0], d[1], d[2], d[3]);
+      };
+      put(fh, v, 0x05040100u);
+      put(fh + plane, v, 0x07060302u);
+      if (fth) {
+        put(fth, vt, 0x05040100u);
+        put(fth + plane, vt, 0x07060302u);
       }
-      if (th_)
-        for (int j = 0; j < 8; ++j) {
-          th_[off + j] = thv[j];
-          tl_[off + j] = tlv[j];
-        }
     }
   }
 }
@@ -409,12 +496,23 @@ void launch_layer_classes(const Model& m, const Work& w, int B, hipStream_t st) 
   hipLaunchKernelGGL(k_layer_classes, dim3(1), dim3(kBlock), 0, st, w, B);
 }
 
+// dynamic LDS of the reduced-precision profile kernel: the path matrix
+static size_t profile_lds_bytes(const Model& m) {
+  return m.mode == kTransmission ? (size_t)m.L_pad * path_ld(m.L_pad) * 4 : 0;
+}
+
+hipError_t profile_configure(const Model& m, bool fp64) {
+  if (fp64) return hipSuccess;
+  return hipFuncSetAttribute((const void*)k_profile<float>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)((size_t)kMaxLayers * path_ld(kMaxLayers) * 4));
+}
+
 void launch_profile(const Model& m, const Work& w, int B, const double* params, const int32_t* n_layers,
                     bool fp64, hipStream_t st) {
   if (fp64) {
-    hipLaunchKernelGGL(k_profile<double>, dim3(B), dim3(kBlock), 0, st, m, w, params, n_layers);
+    hipLaunchKernelGGL(k_profile<double>, dim3(B), dim3(kBlockP), 0, st, m, w, params, n_layers);
   } else {
-    hipLaunchKernelGGL(k_profile<float>, dim3(B), dim3(kBlock), 0, st, m, w, params, n_layers);
+    hipLaunchKernelGGL(k_profile<float>, dim3(B), dim3(kBlockP), profile_lds_bytes(m), st, m, w, params, n_layers);
     if (m.cloud_ng)
       hipLaunchKernelGGL(k_cloud_q, dim3((unsigned)((m.n_nu_pad + kBlock - 1) / kBlock), (unsigned)B), dim3(kBlock), 0,
                          st, m, w);
