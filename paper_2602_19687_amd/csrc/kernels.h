@@ -102,17 +102,20 @@ __device__ inline T wave_sums16(const T (&v)[16], int lane) {
   r += lane_xor<1>(r);
   return r;
 }
-// sum over the wave, every lane gets it (the same tree)
+// sum over the aligned groups of g = 8, 16, 32 or 64 lanes, every lane gets it (the same
+// tree), by lane moves alone
 template <typename T>
-__device__ inline T wave_sum_all(T v) {
-  v += __shfl_xor(v, 32);
-  v += __shfl_xor(v, 16);
-  v += lane_xor<8>(v);
+__device__ inline T group_sum_all(T v, int g) {
+  if (g >= 64) v = halve_add<32>(v, v);
+  if (g >= 32) v = halve_add<16>(v, v);
+  if (g >= 16) v += lane_xor<8>(v);
   v += lane_xor<4>(v);
   v += lane_xor<2>(v);
   v += lane_xor<1>(v);
   return v;
 }
+template <typename T>
+__device__ inline T wave_sum_all(T v) { return group_sum_all(v, 64); }
 
 void launch_profile(const Model& m, const Work& w, int B, const double* params, const int32_t* n_layers,
                     bool fp64, hipStream_t st);

@@ -466,34 +466,45 @@ __global__ __launch_bounds__(kBlock) void k_cloud_q(Model m, Work w) {
   for (int k = 0; k < kCloudSpec; ++k) out[(size_t)(1 + k) * m.n_nu_pad] = dq[k];
 }
 
+constexpr int kBlockClasses = 256;
+
 // Layer-count classes of the call: class 0 holds the samples of at most kShortLayers
 // layers (and invalid samples, which the kernels skip), class 1 the rest; each list is
 // ordered longest first (ties by sample index), so the most expensive work items start
 // first.  One workgroup; a sample's rank counts the samples ahead of it in its class.
-__global__ __launch_bounds__(kBlock) void k_layer_classes(Work w, int B) {
-  for (int b = threadIdx.x; b < B; b += kBlock) {
-    const int lb = w.status[b] ? 0 : w.nlay[b];
-    const int cb = lb > kShortLayers ? 1 : 0;
+__global__ __launch_bounds__(kBlockClasses) void k_layer_classes(Work w, int B) {
+  __shared__ int s_l[kBlockClasses];   // layer counts of a run of samples (0: invalid)
+  auto layers = [&](int q) { return w.status[q] ? 0 : w.nlay[q]; };
+  int n_long = 0;
+  for (int b0 = 0; b0 < B; b0 += kBlockClasses) {
+    const int b = b0 + threadIdx.x;
+    const int lb = b < B ? layers(b) : 0;
+    const bool cb = lb > kShortLayers;
     int rank = 0;
-    for (int q = 0; q < B; ++q) {
-      const int lq = w.status[q] ? 0 : w.nlay[q];
-      if ((lq > kShortLayers ? 1 : 0) == cb && (lq > lb || (lq == lb && q < b))) ++rank;
+    n_long = 0;
+    for (int q0 = 0; q0 < B; q0 += kBlockClasses) {
+      __syncthreads();   // the last run's readers are done
+      if (q0 + (int)threadIdx.x < B) s_l[threadIdx.x] = layers(q0 + threadIdx.x);
+      __syncthreads();
+      const int n = min(kBlockClasses, B - q0);
+      for (int q = 0; q < n; ++q) {
+        const int lq = s_l[q];
+        const bool cq = lq > kShortLayers;
+        n_long += cq;
+        rank += cq == cb && (lq > lb || (lq == lb && q0 + q < b));
+      }
     }
-    w.cls[2 + cb * B + rank] = b;
+    if (b < B) w.cls[2 + (cb ? B : 0) + rank] = b;
   }
-  if (threadIdx.x < 2) {
-    int n = 0;
-    for (int q = 0; q < B; ++q) {
-      const int lq = w.status[q] ? 0 : w.nlay[q];
-      n += (lq > kShortLayers ? 1 : 0) == (int)threadIdx.x;
-    }
-    w.cls[threadIdx.x] = n;
+  if (threadIdx.x == 0) {
+    w.cls[0] = B - n_long;
+    w.cls[1] = n_long;
   }
 }
 
 void launch_layer_classes(const Model& m, const Work& w, int B, hipStream_t st) {
   (void)m;
-  hipLaunchKernelGGL(k_layer_classes, dim3(1), dim3(kBlock), 0, st, w, B);
+  hipLaunchKernelGGL(k_layer_classes, dim3(1), dim3(kBlockClasses), 0, st, w, B);
 }
 
 // dynamic LDS of the reduced-precision profile kernel: the path matrix
