@@ -437,9 +437,23 @@ __global__ __launch_bounds__(kBlockT) void k_ck_trans(Model m, Work w, Tables tb
 // bins of one table row.
 constexpr int kProdBins = kTileNu / kCkG;   // bins per tile
 
+// 32-row blocks of one of two waves: as mblocks_for, costs KBe - 2 mi
+__device__ inline unsigned split_blocks32(int part, int MBe, int KBe) {
+  unsigned mine = 0;
+  int c0 = 0, c1 = 0;
+  for (int mi = 0; mi < MBe; ++mi) {
+    const int cost = KBe - 2 * mi;
+    const bool first = c0 <= c1;
+    if (first == (part == 0)) mine |= 1u << mi;
+    (first ? c0 : c1) += cost;
+  }
+  return mine;
+}
+
 template <int S, bool CIA>
 __global__ __launch_bounds__(kBlockT) void k_ck_trans_prod(Model m, Work w, Tables tb, int B,
                                                            float* __restrict__ spec) {
+  constexpr int kSlots = 3;   // row blocks of a wave: five row blocks in two halves
   extern __shared__ __align__(16) unsigned char lds[];
   const int n_bt = (m.n_nu + kProdBins - 1) / kProdBins;   // bin tiles per sample
   const int logical = xcd_logical_block(blockIdx.x, gridDim.x);
@@ -458,7 +472,7 @@ __global__ __launch_bounds__(kBlockT) void k_ck_trans_prod(Model m, Work w, Tabl
   uint16_t* s_bhi = reinterpret_cast<uint16_t*>(lds);
   uint16_t* s_blo = s_bhi + kTileNu * stride;
   float* s_area = reinterpret_cast<float*>(s_blo + kTileNu * stride);
-  float* s_abs = s_area + Lp;   // [kProdBins][Lp]: combined absorption per bin and chord row
+  float* s_abs = s_area + Lp;   // [kProdBins][Lp]: combined absorption per bin and chord row, after the last pass
   const float* area = reinterpret_cast<const float*>(w.area) + (size_t)b * Lp;
   for (int i = tid; i < Lp; i += kBlockT) s_area[i] = area[i];
 
@@ -484,19 +498,38 @@ __global__ __launch_bounds__(kBlockT) void k_ck_trans_prod(Model m, Work w, Tabl
   const int KBe = (L + 15) >> 4, MBe = (L + 31) >> 5, KB = Lp >> 4;
   const int nb = wv & 3;
   const size_t plane = (size_t)(Lp >> 5) * KB * 512;
-  const uint16_t* fh = w.pfrag + (size_t)b * 2 * plane;
-  const uint16_t* fl = fh + plane;
+  // this sample's P fragments (hi plane, then lo plane), as in the cross-section kernel
+  const __amdgpu_buffer_rsrc_t rs_f = make_rsrc(w.pfrag + (size_t)b * 2 * plane, 2 * plane * 2);
+  const uint32_t lo_plane = (uint32_t)plane * 2u, voff_f = (uint32_t)lane * 16u;
   const int ccol = 32 * nb + (lane & 31);
   const int khalf = 8 * (lane >> 5);
-  const float wg = tb.ckw[lane & 7];
+  const float wg_even = tb.ckw[lane & 6], wg_odd = (lane & 1) ? tb.ckw[lane & 7] : 1.0f;
   const int bin_c = 4 * nb + ((lane & 31) >> 3);   // the tile bin of this lane's MFMA column
+  // row blocks of this wave, cost-balanced between the two waves of a column block
+  int slot_mi[kSlots];
+  {
+    const unsigned mine = split_blocks32(wv >> 2, MBe, KBe);
+    int n = 0;
+    for (int mi = 0; mi < MBe; ++mi)
+      if ((mine & (1u << mi)) && n < kSlots) slot_mi[n++] = mi;
+    for (; n < kSlots; ++n) slot_mi[n] = -1;
+  }
+  // combined absorption of the passes so far, of two rows of each block per lane: rows
+  // q = 2 k + {0, 1} of the 16 MFMA rows, k from the lane's place among its bin's eight
+  float comb[kSlots][2];
+  const bool k1 = lane & 1, k2 = lane & 2, k4 = lane & 4;
 
 #pragma unroll 1
   for (int s = 0; s < S; ++s) {
     // phase A: absorber s's optical depth of every layer at the tile's columns -> bf16
     // hi/lo B operand in LDS
     const float2 cof = *reinterpret_cast<const float2*>(tb.c + (size_t)s * ncol + col);
-    for (int o = wv; o < 2 * KBe; o += kBlockT / 64) {
+    // a contiguous run of layer octets per wave; a layer in the cell of the one before it
+    // reuses its table entries
+    float2 t00, t10, t01, t11;
+    float ca[2], cb[2];
+    int cell_prev = -1;
+    for (int o = 2 * KBe * wv / (kBlockT / 64); o < 2 * KBe * (wv + 1) / (kBlockT / 64); ++o) {
       float e0[8], e1[8];
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
@@ -505,14 +538,27 @@ __global__ __launch_bounds__(kBlockT) void k_ck_trans_prod(Model m, Work w, Tabl
         if (l < L) {
           const float* rl = rec + (size_t)l * RL;
           const int cl = cells[l];
-          const int it = cl & 255, ip = (cl >> 8) & 255, itc = cl >> 16;
+          if (cl != cell_prev) {
+            const int it = cl & 255, ip = (cl >> 8) & 255, itc = cl >> 16;
+            const uint32_t row = (uint32_t)((s * m.n_t + it) * m.n_p + ip) * row_bytes;
+            t00 = load_f32x2(rh, vo, row);
+            t10 = load_f32x2(rh, vo, row + tstep);
+            t01 = load_f32x2(rh, vo, row + row_bytes);
+            t11 = load_f32x2(rh, vo, row + tstep + row_bytes);
+            if (CIA && s == 0) {
+#pragma unroll
+              for (int p = 0; p < 2; ++p) {
+                const uint32_t rowc = (uint32_t)(p * m.n_tc + itc) * (uint32_t)npad * 4u;
+                ca[p] = load_f32(rhc, (uint32_t)j * 4u, rowc);
+                cb[p] = load_f32(rhc, (uint32_t)j * 4u, rowc + (uint32_t)npad * 4u);
+              }
+            }
+            cell_prev = cl;
+          }
           const float wt = rl[0], wp = rl[1];
           const float w11 = wt * wp, w10 = wt - w11, w01 = wp - w11, w00 = 1.0f - wt - wp + w11;
-          const uint32_t row = (uint32_t)((s * m.n_t + it) * m.n_p + ip) * row_bytes;
           const float lam = rl[kRecFixed + s];
           float v0 = cof.x + lam, v1 = cof.y + lam;
-          const float2 t00 = load_f32x2(rh, vo, row), t10 = load_f32x2(rh, vo, row + tstep);
-          const float2 t01 = load_f32x2(rh, vo, row + row_bytes), t11 = load_f32x2(rh, vo, row + tstep + row_bytes);
           v0 = fmaf(w00, t00.x, v0);
           v1 = fmaf(w00, t00.y, v1);
           v0 = fmaf(w10, t10.x, v0);
@@ -530,11 +576,9 @@ __global__ __launch_bounds__(kBlockT) void k_ck_trans_prod(Model m, Work w, Tabl
               const float wtc = rl[2];
 #pragma unroll
               for (int p = 0; p < 2; ++p) {
-                const uint32_t rowc = (uint32_t)(p * m.n_tc + itc) * (uint32_t)npad * 4u;
-                const uint32_t vj = (uint32_t)j * 4u;
                 float v = cc[p] + rl[5 + p];
-                v = fmaf(1.0f - wtc, load_f32(rhc, vj, rowc), v);
-                v = fmaf(wtc, load_f32(rhc, vj, rowc + (uint32_t)npad * 4u), v);
+                v = fmaf(1.0f - wtc, ca[p], v);
+                v = fmaf(wtc, cb[p], v);
                 dc += exp2_fast(v);
               }
             }
@@ -560,37 +604,81 @@ __global__ __launch_bounds__(kBlockT) void k_ck_trans_prod(Model m, Work w, Tabl
     }
     __syncthreads();
 
-    // phase B: tau = P dtau; wave wv owns 32-column block nb and half (wv >> 2) of the row blocks
-    for (int mi = (wv >> 2); mi < MBe; mi += 2) {
-      f32x16 acc = {};
-      for (int kb = 2 * mi; kb < KBe; ++kb) {
-        const size_t fo = ((size_t)(mi * KB + kb) * 64 + lane) * 8;
-        const bf16x8 ah = *reinterpret_cast<const bf16x8*>(fh + fo);
-        const bf16x8 al = *reinterpret_cast<const bf16x8*>(fl + fo);
-        const bf16x8 bh = *reinterpret_cast<const bf16x8*>(s_bhi + ccol * stride + 16 * kb + khalf);
-        const bf16x8 bl = *reinterpret_cast<const bf16x8*>(s_blo + ccol * stride + 16 * kb + khalf);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, bh, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bl, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bh, acc, 0, 0, 0);
-      }
-      // phase C: per row, absorber s's g-weighted absorption in its bin (8 lanes),
-      // combined into the bin's running absorption
+    // phase B: tau = P dtau over this wave's row blocks
 #pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        float a = wg * one_minus_exp(acc[q], exp2_fast(-1.4426950408889634f * acc[q]));
-        a += __shfl_xor(a, 1);
-        a += __shfl_xor(a, 2);
-        a += __shfl_xor(a, 4);
-        const int r = 32 * mi + 8 * (q >> 2) + 4 * (lane >> 5) + (q & 3);
-        if ((lane & 7) == 0) {
-          float* pa = s_abs + bin_c * Lp + r;
-          const float prev = s == 0 ? 0.0f : *pa;
-          *pa = prev + a - prev * a;
+    for (int q2 = 0; q2 < kSlots; ++q2) {
+      const int mi = slot_mi[q2];
+      if (mi < 0) continue;
+      f32x16 acc = {};
+      // fragments in two groups of two K blocks, one group in flight (blocks past KBe read
+      // the next row block's, or zeros past the range, and are never used)
+      bf16x8 ga[2][2], gb[2][2];
+      auto load = [&](bf16x8 (&gr)[2][2], int k) {
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+          for (int y = 0; y < 2; ++y)
+            gr[x][y] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
+                                                      rs_f, voff_f, (uint32_t)(mi * KB + k + x) * 1024u + (y ? lo_plane : 0u), 0));
+      };
+      auto product = [&](const bf16x8 (&gr)[2][2], int k0) {
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+          const int kb = k0 + x;
+          if (kb >= KBe) break;
+          const bf16x8 bh = *reinterpret_cast<const bf16x8*>(s_bhi + ccol * stride + 16 * kb + khalf);
+          const bf16x8 bl = *reinterpret_cast<const bf16x8*>(s_blo + ccol * stride + 16 * kb + khalf);
+          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(gr[x][1], bh, acc, 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(gr[x][0], bl, acc, 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(gr[x][0], bh, acc, 0, 0, 0);
         }
+      };
+      load(ga, 2 * mi);
+#pragma unroll 1
+      for (int kb = 2 * mi; kb < KBe; kb += 4) {
+        load(gb, kb + 2);
+        product(ga, kb);
+        if (kb + 2 >= KBe) break;
+        load(ga, kb + 4);
+        product(gb, kb + 2);
+      }
+      // phase C: per row, absorber s's g-weighted absorption in its bin: the 16 rows summed
+      // over the bin's eight lanes by halving exchanges (lane ^ 1, 2, 4), so each lane ends
+      // with two rows, which it combines into the bin's running absorption
+      // (a pair of lanes adds w x of the even g-point, fused, to the rounded w x of the odd)
+      float a[16], h8[8], h4[4];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) a[q] = wg_odd * one_minus_exp(acc[q], exp2_fast(-1.4426950408889634f * acc[q]));
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const float keep = k1 ? a[q + 8] : a[q], recv = lane_xor<1>(k1 ? a[q] : a[q + 8]);
+        h8[q] = fmaf(wg_even, k1 ? recv : keep, k1 ? keep : recv);
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) h4[q] = (k2 ? h8[q + 4] : h8[q]) + lane_xor<2>(k2 ? h8[q] : h8[q + 4]);
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const float av = (k4 ? h4[q + 2] : h4[q]) + lane_xor<4>(k4 ? h4[q] : h4[q + 2]);
+        const float prev = s == 0 ? 0.0f : comb[q2][q];
+        comb[q2][q] = fmaf(-prev, av, prev + av);
       }
     }
     __syncthreads();   // the next pass overwrites the B operand
   }
+  // MFMA row q of block mi is row 32 mi + 8 (q / 4) + 4 (lane / 32) + q % 4
+  {
+    const int q0 = (k1 ? 8 : 0) + (k2 ? 4 : 0) + (k4 ? 2 : 0);
+#pragma unroll
+    for (int q2 = 0; q2 < kSlots; ++q2) {
+      if (slot_mi[q2] < 0) continue;
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const int r = 32 * slot_mi[q2] + 8 * (q0 >> 2) + 4 * (lane >> 5) + ((q0 & 3) + q);
+        s_abs[bin_c * Lp + r] = comb[q2][q];
+      }
+    }
+  }
+  __syncthreads();
   // the bins' combined absorption, annulus-weighted and summed over the rows: 32
   // threads per bin
   const int bj = tid >> 5;
