@@ -679,8 +679,8 @@ __global__ __launch_bounds__(kBlockT) void k_trans_adj_fp64(Model m, Work w, Tab
   const bool act = lane < TILE;                    // this lane holds a wavenumber of the tile
   for (int i = tid; i < R * 16; i += kBlockT) s_sums[i] = 0.0;
 
-  const double* rec = reinterpret_cast<const double*>(w.rec) + (size_t)b * Lp * rec_len(S);
-  const int32_t* cells = w.cells + (size_t)b * Lp;
+  const auto rec = const_ptr(reinterpret_cast<const double*>(w.rec)) + (size_t)b * Lp * rec_len(S);
+  const auto cells = const_ptr(w.cells) + (size_t)b * Lp;
   const double* pm = w.pm64 + (size_t)b * Lp * Lp;
   const double* area = reinterpret_cast<const double*>(w.area) + (size_t)b * Lp;
   for (int i = tid; i < R; i += kBlockT) s_area[i] = area[i];
@@ -837,7 +837,7 @@ __global__ __launch_bounds__(kBlockT) void k_trans_adj_fp64(Model m, Work w, Tab
           fetch_rows64<S, CIA>(m, tb, cl, nu, rows);
           cell_prev = cl;
         }
-        const double* rl = rec + (size_t)l * rec_len(S);
+        const auto rl = rec + (size_t)l * rec_len(S);
         double t[S + 2], dw[S + 2], v[16];
         eval_rows64_deriv<S, CIA>(rl, rows, t, dw);
 #pragma unroll

@@ -493,8 +493,8 @@ __global__ __launch_bounds__(kBlockT) void k_ck_trans_prod(Model m, Work w, Tabl
     cc[1] = tb.cc[npad + j];
   }
   constexpr int RL = rec_len(S);
-  const float* rec = reinterpret_cast<const float*>(w.rec) + (size_t)b * Lp * RL;
-  const int32_t* cells = w.cells + (size_t)b * Lp;
+  const auto rec = const_ptr(reinterpret_cast<const float*>(w.rec)) + (size_t)b * Lp * RL;
+  const auto cells = const_ptr(w.cells) + (size_t)b * Lp;
   const int KBe = (L + 15) >> 4, MBe = (L + 31) >> 5, KB = Lp >> 4;
   const int nb = wv & 3;
   const size_t plane = (size_t)(Lp >> 5) * KB * 512;
@@ -536,7 +536,7 @@ __global__ __launch_bounds__(kBlockT) void k_ck_trans_prod(Model m, Work w, Tabl
         const int l = 8 * o + q;
         float d0 = 0.0f, d1 = 0.0f;
         if (l < L) {
-          const float* rl = rec + (size_t)l * RL;
+          const auto rl = rec + (size_t)l * RL;
           const int cl = cells[l];
           if (cl != cell_prev) {
             const int it = cl & 255, ip = (cl >> 8) & 255, itc = cl >> 16;

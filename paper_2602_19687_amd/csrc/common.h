@@ -157,4 +157,14 @@ struct Tables {
   const double* cke;     // correlated-k: [kCkG] upper edges of the g-intervals (running sums of the pair weights)
 };
 
+// A pointer to data that no kernel of this launch writes, in the constant address space:
+// uniform reads through it are scalar loads.  (Past a barrier the compiler otherwise reads
+// uniform data by vector loads, whose latency then stands in front of every layer.)
+template <typename T>
+using ConstPtr = const __attribute__((address_space(4))) T*;
+template <typename T>
+__device__ inline ConstPtr<T> const_ptr(const T* p) {
+  return (ConstPtr<T>)p;
+}
+
 }  // namespace exofwd

@@ -38,9 +38,9 @@ __global__ __launch_bounds__(kBlock) void k_emission_fp64(Model m, Work w, Table
     return;
   }
   const int L = w.nlay[b];
-  const double* rec = reinterpret_cast<const double*>(w.rec) + (size_t)b * Lp * rec_len(S);
-  const int32_t* cells = w.cells + (size_t)b * Lp;
-  const double* t_lev = w.t_lev + (size_t)b * (Lp + 1);
+  const auto rec = const_ptr(reinterpret_cast<const double*>(w.rec)) + (size_t)b * Lp * rec_len(S);
+  const auto cells = const_ptr(w.cells) + (size_t)b * Lp;
+  const auto t_lev = const_ptr(w.t_lev) + (size_t)b * (Lp + 1);
   const int nu = nu0 + lane;
   const double nud = m.nu[nu];
   const double c1n3 = 2.0 * kHpl * kC * kC * nud * nud * nud;

@@ -270,7 +270,7 @@ __global__ __launch_bounds__(kBlock) void k_emis_adj_fp64(Model m, Work w, AdjWo
   const double* dt = aw.dtau64 + (size_t)b * Lp * npad + nu;
   double* dtb = aw.dtb64 + (size_t)b * Lp * npad + nu;
   double* ps = aw.psum64 + ((size_t)b * m.n_tiles64 + tile) * (Lp + 1);
-  const double* t_lev = w.t_lev + (size_t)b * (Lp + 1);
+  const auto t_lev = const_ptr(w.t_lev) + (size_t)b * (Lp + 1);
   const int kb = w.bin_of[nu];
   const double nd = m.nu[nu];
   double seed = 0.0;

@@ -347,8 +347,8 @@ __device__ inline void fetch_rows64(const Model& m, const Tables& tb, int cl, in
 
 // Optical depth of one layer (record rl) from its table entries; qext multiplies the cloud
 // column (1 for the grey deck).  The bilinear weights carry the factor log2(10).
-template <int S, bool CIA>
-__device__ inline double eval_rows64(const double* __restrict__ rl, const LayerRows64<S, CIA>& r, double nu4,
+template <int S, bool CIA, typename Rec>
+__device__ inline double eval_rows64(Rec rl, const LayerRows64<S, CIA>& r, double nu4,
                                      double qext) {
   const double wt = rl[0], wp = rl[1];
   const double a = (1.0 - wp) * kLog2_10, b = wp * kLog2_10;
@@ -372,8 +372,8 @@ __device__ inline double eval_rows64(const double* __restrict__ rl, const LayerR
 
 // Line and CIA terms t of one layer with the derivative dw of each exponent with respect
 // to its T weight (log2 units), formed from the differences of the table entries.
-template <int S, bool CIA>
-__device__ inline void eval_rows64_deriv(const double* __restrict__ rl, const LayerRows64<S, CIA>& r, double* t,
+template <int S, bool CIA, typename Rec>
+__device__ inline void eval_rows64_deriv(Rec rl, const LayerRows64<S, CIA>& r, double* t,
                                          double* dw) {
   const double wt = rl[0], a = (1.0 - rl[1]) * kLog2_10, b = rl[1] * kLog2_10;
 #pragma unroll

@@ -322,8 +322,8 @@ __global__ __launch_bounds__(kBlockT) void k_trans_fwd_fp64(Model m, Work w, Tab
   const int L = w.nlay[b], MB = (L + 15) >> 4;
   double* s_dt = reinterpret_cast<double*>(lds);           // [rows16(L_max)][kLd64]
   double* s_red = s_dt + (size_t)rows16(m.L_max) * kLd64;  // [2][64]
-  const double* rec = reinterpret_cast<const double*>(w.rec) + (size_t)b * Lp * rec_len(S);
-  const int32_t* cells = w.cells + (size_t)b * Lp;
+  const auto rec = const_ptr(reinterpret_cast<const double*>(w.rec)) + (size_t)b * Lp * rec_len(S);
+  const auto cells = const_ptr(w.cells) + (size_t)b * Lp;
   const int nu = nu0 + lane;
   const double nu4 = tb.nu4d[nu];
   // grey deck: the record holds the optical depth; non-grey: the column times Q_ext(nu)
