@@ -616,8 +616,21 @@ __global__ __launch_bounds__(kBlock) void k_cloud_spectral(Model m, Work w, AdjW
   for (int tile = t0; tile < t1; ++tile) {
     const int nu = tile * kTileNu + 2 * lane;
     float g0 = 0.0f, g1 = 0.0f;
-    // rows below the opaque frontier are zero (and not stored)
-    for (int l = 32 * w.front[(size_t)b * m.n_tiles + tile]; l < L; ++l) {
+    // rows below the opaque frontier are zero (and not stored); kFly rows in flight
+    constexpr int kFly = 8;
+    int l = 32 * w.front[(size_t)b * m.n_tiles + tile];
+    for (; l + kFly <= L; l += kFly) {
+      float2 d[kFly];
+#pragma unroll
+      for (int u = 0; u < kFly; ++u) d[u] = *reinterpret_cast<const float2*>(dtb + (size_t)(l + u) * npad + nu);
+#pragma unroll
+      for (int u = 0; u < kFly; ++u) {
+        const float dl = rec[(size_t)(l + u) * rec_len_wide(m.S) + 4];
+        g0 = fmaf(dl, d[u].x, g0);
+        g1 = fmaf(dl, d[u].y, g1);
+      }
+    }
+    for (; l < L; ++l) {
       const float dl = rec[(size_t)l * rec_len_wide(m.S) + 4];
       const float2 d = *reinterpret_cast<const float2*>(dtb + (size_t)l * npad + nu);
       g0 = fmaf(dl, d.x, g0);
@@ -926,26 +939,22 @@ __global__ __launch_bounds__(kBlockT) void k_trans_adj_fp64(Model m, Work w, Tab
 // FP64 chain: one workgroup per sample
 constexpr int kBlockC = 512, kWavesC = kBlockC / 64;
 
-// derivatives of P_il with respect to r_l, r_{l+1} and b_i (l > i), or the
-// full derivatives with respect to r_i, r_{i+1} on the diagonal
-__device__ inline void path_derivs(const double* r, int i, int l, double& d_lo, double& d_up, double& d_b) {
-  if (l == i) {
-    const double dr = r[i + 1] - r[i];
-    const double q = (3.0 * r[i + 1] + r[i]) / dr;
-    const double sq = sqrt(q);
-    d_up = (3.0 - q) / (2.0 * dr * sq);
-    d_lo = (1.0 + q) / (2.0 * dr * sq);
-    d_b = 0.0;
-    return;
-  }
-  const double bb = 0.5 * (r[i] + r[i + 1]);
-  const double rup = r[l + 1], rlo = r[l];
-  const double sup = sqrt((rup - bb) * (rup + bb)), slo = sqrt((rlo - bb) * (rlo + bb));
-  const double iup = rcp_d(sup), ilo = rcp_d(slo), iden = rcp_d(sup + slo);
+// derivatives of P_il with respect to r_l, r_{l+1} and b_i, l > i: bb = b_i, rlo and rup
+// the layer's levels
+__device__ inline void path_derivs(double bb, double rlo, double rup, double& d_lo, double& d_up, double& d_b) {
+  const double xu = (rup - bb) * (rup + bb), xl = (rlo - bb) * (rlo + bb);
+  const double iup = rsq_d(xu), ilo = rsq_d(xl);
+  const double iden = rcp_d(fma(xu, iup, xl * ilo));
   const double f = 2.0 * (rup + rlo) * iden * iden;
-  d_up = 2.0 * iden - f * rup * iup;
-  d_lo = 2.0 * iden - f * rlo * ilo;
+  d_up = fma(-f * rup, iup, 2.0 * iden);
+  d_lo = fma(-f * rlo, ilo, 2.0 * iden);
   d_b = f * bb * (iup + ilo);
+}
+// the diagonal's full derivatives with respect to r_i, r_{i+1}
+__device__ inline void path_derivs_diag(double rlo, double rup, double& d_lo, double& d_up) {
+  const double dr = rup - rlo, q = (3.0 * rup + rlo) / dr, sq = sqrt(q);
+  d_up = (3.0 - q) / (2.0 * dr * sq);
+  d_lo = (1.0 + q) / (2.0 * dr * sq);
 }
 
 // Slopes of the monotone cubic Hermite interpolant through (xk, yk) and their
@@ -1025,8 +1034,8 @@ __device__ inline void wave_scan(int lane, int n, bool rev, Get get, double* out
 // Bound by latency (one workgroup per sample): sums over the block are 16 at a time (a wave
 // by halving exchanges, then the waves), the hydrostatic recursion is four scans, and the
 // chunks of every partial sum have been added by k_reduce_chunks.  One sample of 100
-// layers and 30000 wavenumbers: 157 -> 32 us (1024 samples 392 -> 123 us; 64 samples of up
-// to 150 layers and 400000 wavenumbers 728 -> 48 us), the chunk sums 58 -> 12 us.
+// layers and 30000 wavenumbers: 157 -> 21 us (1024 samples 392 -> 80 us; 64 samples of up
+// to 150 layers and 400000 wavenumbers 728 -> 29 us), the chunk sums 58 -> 12 us.
 template <typename PbarT>
 __global__ __launch_bounds__(kBlockC) void k_chain(Model m, Work w, AdjWork aw, int C, const double* __restrict__ params,
                                                    const uint8_t* __restrict__ mask, double* __restrict__ grad) {
@@ -1040,14 +1049,16 @@ __global__ __launch_bounds__(kBlockC) void k_chain(Model m, Work w, AdjWork aw, 
   }
   const int L = w.nlay[b];
   // virtual sample b of real sample real_sample(m, b); a clear one has no cloud terms
-  const double* th = params + (size_t)real_sample(m, b) * m.P;
+  __shared__ double s_th[kMaxParams];
+  const double* th = s_th;
   const bool cloudy = m.has_cloud && !clear_sample(m, b);
   const bool ng = m.cloud_ng && cloudy;
   const bool trans = m.mode == kTransmission;
-  constexpr int kMaxSeg = 8;
+  constexpr int kRowChunk = 16, kChunks = kMaxLayers / kRowChunk, kColBlocks = (kMaxLayers + 63) / 64;
   __shared__ double s_r[kMaxLayers + 1], s_ub[kMaxLayers + 1], s_scan[4][kMaxLayers + 1];
   __shared__ double s_t[kMaxLayers], s_tb[kMaxLayers], s_lndr[kMaxLayers];
-  __shared__ double s_plo[kMaxSeg * kMaxLayers], s_pup[kMaxSeg * kMaxLayers], s_pb[kMaxSeg * kMaxLayers];
+  // path-matrix adjoint: column sums per chunk of rows, row sums per block of columns
+  __shared__ double s_plo[kChunks][kMaxLayers], s_pup[kChunks][kMaxLayers], s_pb[kColBlocks][kMaxLayers];
   __shared__ double s_w[2][kWavesC][16], s_sum[2][16], s_x[kMaxSpecies];
   __shared__ double s_kx[kMaxKnots], s_ky[kMaxKnots], s_kd[kMaxKnots], s_kj[kMaxKnots * kMaxKnots];
   __shared__ int s_above;
@@ -1058,8 +1069,9 @@ __global__ __launch_bounds__(kBlockC) void k_chain(Model m, Work w, AdjWork aw, 
   const double ln10 = 2.302585092994045684017991454684;
   const double dlnp = -step * ln10;
   auto logp_lev = [&](int j) { return j == L ? m.log10_ptop : m.log10_pbot + j * step; };
-  const double lpref = log10(m.p_ref / kBar);
+  const double lpref = m.log10_pref;
   if (tid == 0) s_above = 0;
+  if (tid < m.P) s_th[tid] = params[(size_t)real_sample(m, b) * m.P + tid];
   __syncthreads();
   for (int j = tid; j <= L; j += kBlockC) {
     s_r[j] = rl[j];
@@ -1150,22 +1162,10 @@ __global__ __launch_bounds__(kBlockC) void k_chain(Model m, Work w, AdjWork aw, 
     // dT from n = p/kT and from the table weights (interior cells only)
     double tbar = -lnn_bar / t;
     const double ln2 = 0.69314718055994530941723212145818;
-    if (t > m.t_grid[0] && t < m.t_grid[m.n_t - 1]) {
-      int lo = 0, hi = m.n_t - 1;
-      while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (m.t_grid[mid] <= t) lo = mid; else hi = mid;
-      }
-      tbar += ln2 * ex[0] / (m.t_grid[lo + 1] - m.t_grid[lo]);
-    }
-    if (m.has_cia && t > m.tc_grid[0] && t < m.tc_grid[m.n_tc - 1]) {
-      int lo = 0, hi = m.n_tc - 1;
-      while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (m.tc_grid[mid] <= t) lo = mid; else hi = mid;
-      }
-      tbar += ln2 * ex[3] / (m.tc_grid[lo + 1] - m.tc_grid[lo]);
-    }
+    const int cell = w.cells[(size_t)b * Lp + l], it = cell & 255, itc = cell >> 16;
+    if (t > m.t_grid[0] && t < m.t_grid[m.n_t - 1]) tbar += ln2 * ex[0] / (m.t_grid[it + 1] - m.t_grid[it]);
+    if (m.has_cia && t > m.tc_grid[0] && t < m.tc_grid[m.n_tc - 1])
+      tbar += ln2 * ex[3] / (m.tc_grid[itc + 1] - m.tc_grid[itc]);
     s_tb[l] = tbar;
 #pragma unroll
     for (int s = 0; s < kMaxSpecies; ++s) va[s] += sm[s];
@@ -1194,41 +1194,63 @@ __global__ __launch_bounds__(kBlockC) void k_chain(Model m, Work w, AdjWork aw, 
   wave_part(0, va);
   wave_part(1, vb);
 
-  // path-matrix adjoint: column pass (r_l, r_{l+1}) and row pass (b_i); four entries'
-  // loads are issued together.  Each column's (row's) entries are split into nseg
-  // contiguous segments on different threads (the longest column set the pace of the
-  // whole block); the segments' partial sums are added in segment order
+  // path-matrix adjoint: column sums (r_l, r_{l+1}) and row sums (b_i).  A wave takes 64
+  // columns, one a lane, and 16 rows, each entry's derivatives formed once: the column
+  // sums stay in the lanes, the rows' sums meet over the wave.
   const PbarT* pbar = reinterpret_cast<const PbarT*>(aw.pbar) + (size_t)b * C * Lp * Lp;
-  constexpr int nseg = kMaxSeg;
-  for (int t = tid; t < (trans ? 2 * nseg * L : 0); t += kBlockC) {
-    const bool column = t < nseg * L;
-    const int u = column ? t : t - nseg * L;
-    const int x = u % L, sg = u / L;
-    // a column's rows i <= x, or a row's columns l > x
-    const int first = column ? 0 : x + 1, n = column ? x + 1 : L - 1 - x;
-    const int qa = first + sg * n / nseg, qb = first + (sg + 1) * n / nseg;
-    double a0 = 0.0, a1 = 0.0;
-    for (int q0 = qa; q0 < qb; q0 += 4) {
-      double p[4];
+  const int n_rc = (L + kRowChunk - 1) / kRowChunk, n_cb = (L + 63) / 64;
+#pragma unroll 1
+  for (int t = wv; t < (trans ? n_rc * n_cb : 0); t += kWavesC) {
+    const int rc = t % n_rc, cb = t / n_rc, i0 = kRowChunk * rc, x = 64 * cb + lane;
+    if (64 * cb + 63 < i0) continue;   // rows below these columns (never read)
+    const int xc = min(x, L - 1);
+    const double rlo = s_r[xc], rup = s_r[xc + 1];
+    double lo = 0.0, up = 0.0;
+    constexpr int kRows = 4;   // rows in a step, the next step's entries in flight
+    auto entry = [&](int i) { return pbar[(size_t)min(i, L - 1) * Lp + xc]; };
+    PbarT p[kRows];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int q = min(q0 + k, qb - 1);
-        p[k] = (double)pbar[column ? (size_t)q * Lp + x : (size_t)x * Lp + q];
+    for (int k = 0; k < kRows; ++k) p[k] = entry(i0 + k);
+#pragma unroll 1
+    for (int g = i0; g < i0 + kRowChunk; g += kRows) {
+      PbarT cur[kRows];
+      double row[kRows];
+#pragma unroll
+      for (int k = 0; k < kRows; ++k) {
+        cur[k] = p[k];
+        p[k] = entry(g + kRows + k);
       }
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        if (q0 + k >= qb) break;
+      for (int k = 0; k < kRows; ++k) {
+        const int i = min(g + k, L - 1);
+        const bool on = x < L && g + k < x;   // above the diagonal
+        const double r0 = s_r[i], r1 = s_r[i + 1];
         double dlo, dup, db;
-        path_derivs(s_r, column ? q0 + k : x, column ? x : q0 + k, dlo, dup, db);
-        a0 = fma(p[k], column ? dlo : db, a0);
-        a1 = fma(p[k], dup, a1);
+        // lanes that are off take a level pair that is above this one
+        path_derivs(0.5 * (r0 + r1), on ? rlo : r1, on ? rup : 2.0 * r1, dlo, dup, db);
+        const double pk = on ? (double)cur[k] : 0.0;
+        lo = fma(pk, dlo, lo);
+        up = fma(pk, dup, up);
+        row[k] = pk * db;
       }
+      // the four rows' sums over the wave: the lanes of quarter q (lane / 16) get row q's
+      double v = halve_add<16>(halve_add<32>(row[0], row[2]), halve_add<32>(row[1], row[3]));
+      v += lane_xor<8>(v);
+      v += lane_xor<4>(v);
+      v += lane_xor<2>(v);
+      v += lane_xor<1>(v);
+      if ((lane & 15) == 0 && g + (lane >> 4) < L) s_pb[cb][g + (lane >> 4)] = v;
     }
-    if (column) {
-      s_plo[sg * kMaxLayers + x] = a0;
-      s_pup[sg * kMaxLayers + x] = a1;
-    } else {
-      s_pb[sg * kMaxLayers + x] = a0;
+    if (x < L) {
+      if (x >= i0 && x < i0 + kRowChunk) {
+        double dlo, dup;
+        path_derivs_diag(rlo, rup, dlo, dup);
+        const double pd = (double)pbar[(size_t)x * Lp + x];
+        lo = fma(pd, dlo, lo);
+        up = fma(pd, dup, up);
+      }
+      s_plo[rc][x] = lo;
+      s_pup[rc][x] = up;
     }
   }
   __syncthreads();
@@ -1238,16 +1260,15 @@ __global__ __launch_bounds__(kBlockC) void k_chain(Model m, Work w, AdjWork aw, 
   for (int j = tid; j <= L; j += kBlockC) {
     double rb = 0.0;
     if (trans) {
+      // a column's rows end at its own, a row's columns begin at its own
       double lo = 0.0, up = 0.0, bb = 0.0;
-      for (int sg = 0; sg < nseg; ++sg) {
-        if (j < L) {
-          lo += s_plo[sg * kMaxLayers + j];
-          bb += s_pb[sg * kMaxLayers + j];
-        }
-        if (j >= 1) {
-          up += s_pup[sg * kMaxLayers + j - 1];
-          bb += s_pb[sg * kMaxLayers + j - 1];
-        }
+      if (j < L) {
+        for (int k = 0; k <= j / kRowChunk; ++k) lo += s_plo[k][j];
+        for (int k = j / 64; k < n_cb; ++k) bb += s_pb[k][j];
+      }
+      if (j >= 1) {
+        for (int k = 0; k <= (j - 1) / kRowChunk; ++k) up += s_pup[k][j - 1];
+        for (int k = (j - 1) / 64; k < n_cb; ++k) bb += s_pb[k][j - 1];
       }
       const double* ab = aw.abar + (size_t)b * C * Lp;
       const double ab_j = j < L ? ab[j] : 0.0, ab_jm = j >= 1 ? ab[j - 1] : 0.0;
@@ -1332,16 +1353,23 @@ __global__ __launch_bounds__(kBlockC) void k_chain(Model m, Work w, AdjWork aw, 
       }
     }
   };
-  for (int l = tid; l < L; l += kBlockC) {
-    double tb = s_tb[l];
-    if (l < lref) tb += kk * dlnp * s_scan[0][l];
-    else if (l > lref) tb -= kk * dlnp * s_scan[1][l + 1];
-    else tb += kk * (a1 * s_scan[0][lref] - a2 * s_scan[1][lref + 1]);
-    tp_grad(0.5 * (logp_lev(l) + logp_lev(l + 1)), s_t[l], tb);
-  }
-  if (!trans) {
-    const double* tlev = w.t_lev + (size_t)b * (Lp + 1);
-    for (int j = tid; j <= L; j += kBlockC) tp_grad(logp_lev(j), tlev[j], aw.pred[(size_t)b * (Lp + 1) + j]);
+  // layers, then (emission) levels: one copy of the profiles' code
+  for (int q = tid; q < L + (trans ? 0 : L + 1); q += kBlockC) {
+    double lp, t, tb;
+    if (q < L) {
+      tb = s_tb[q];
+      if (q < lref) tb += kk * dlnp * s_scan[0][q];
+      else if (q > lref) tb -= kk * dlnp * s_scan[1][q + 1];
+      else tb += kk * (a1 * s_scan[0][lref] - a2 * s_scan[1][lref + 1]);
+      lp = 0.5 * (logp_lev(q) + logp_lev(q + 1));
+      t = s_t[q];
+    } else {
+      const size_t j = (size_t)b * (Lp + 1) + (q - L);
+      tb = aw.pred[j];
+      lp = logp_lev(q - L);
+      t = w.t_lev[j];
+    }
+    tp_grad(lp, t, tb);
   }
   // s_w[0] was last read before the barriers above; the totals in s_sum[1] (cloud, offset)
   // and s_sum[0] (chemistry) stay, so this set's totals go to s_tp

@@ -24,6 +24,8 @@ constexpr int kMaxLayers = 160;   // L_max; padded layer count is a multiple of 
 constexpr int kLsGroup = 3;       // most layers in one layer-sum group
 constexpr int kMaxKnots = 8;
 constexpr int kMaxMu = 8;
+constexpr int kMaxAxis = 255;     // points of a table axis
+constexpr int kMaxParams = 40;    // parameters of a sample (7 T-p + 8 species + 10 cloud + fraction + 2 + scale + offset)
 constexpr int kTileNu = 128;      // wavenumbers per tile of the reduced-precision transmission kernels
 constexpr int kTile64 = 64;       // wavenumbers per tile of the FP64 and emission kernels
 // cache policy of a buffer access that streams data read or written once (the
@@ -83,7 +85,7 @@ struct Model {
   double bd_dist;           // its distance [cm]
   int ck;                   // correlated-k tables: n_nu spectral bins of kCkG g-points (reduced precision)
   int ck_mix;               // their mixing (kCkRorr)
-  double mu_fixed, log10_pbot, log10_ptop, p_ref, r_p, r_s, g_ref;
+  double mu_fixed, log10_pbot, log10_ptop, log10_pref, p_ref, r_p, r_s, g_ref;
   double kappa_ir, f_hem, kappa_cloud, t_star, dilution, err_c, ray_h2, ray_he;
   double mass[kMaxSpecies];
   double mu_nodes[kMaxMu], mu_weights[kMaxMu];

@@ -427,6 +427,7 @@ exofwd_status exofwd_create(const exofwd_config* cfg, exofwd_ctx** out) {
   m.log10_pbot = std::log10(g.p_bot_bar);
   m.log10_ptop = std::log10(g.p_top_bar);
   m.p_ref = g.p_ref_bar * kBar;
+  m.log10_pref = std::log10(m.p_ref / kBar);
   m.r_p = g.r_p;
   m.r_s = g.r_s;
   m.g_ref = g.g_ref;

@@ -292,6 +292,13 @@ __device__ inline double exp2_q(double f) {
   q = fma(q, f, 0.24022650695910097);
   return fma(q, f, 0.6931471805599453);
 }
+// 1 / sqrt(x) to the last digit or two (x > 0 normal): two Newton steps
+__device__ inline double rsq_d(double x) {
+  double r = __builtin_amdgcn_rsq(x);
+  const double h = 0.5 * x;
+  r = fma(r, fma(-h * r, r, 0.5), r);
+  return fma(r, fma(-h * r, r, 0.5), r);
+}
 // 2^x for finite x (0 or infinity past the exponent range)
 __device__ inline double exp2_d(double x) {
   const double n = __builtin_rint(x), f = x - n;

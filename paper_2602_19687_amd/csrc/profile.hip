@@ -3,6 +3,7 @@
 // areas.  One workgroup of 512 threads per sample.
 #include "cloud.h"
 #include "kernels.h"
+#include "opacity.h"
 #include "tp.h"
 
 namespace exofwd {
@@ -82,6 +83,11 @@ __device__ inline float bf16_to_f(uint16_t h) { return __uint_as_float((uint32_t
 template <typename Put>
 __device__ inline void path_entries(const double* r, const double* dr, int i, int l0, int l1, Put put) {
   const double b = 0.5 * (r[i] + r[i + 1]);
+  // sqrt(r^2 - b^2)
+  auto leg = [&](double rl) {
+    const double x = (rl - b) * (rl + b);
+    return x * rsq_d(x);
+  };
   int l = l0;
   if (l == i) {
     double sup = sqrt(0.5 * dr[i] * (r[i + 1] + b));
@@ -89,10 +95,11 @@ __device__ inline void path_entries(const double* r, const double* dr, int i, in
     ++l;
   }
   if (l >= l1) return;
-  double rlo = r[l], slo = sqrt((rlo - b) * (rlo + b));
+  double rlo = r[l], slo = leg(rlo);
+#pragma unroll 1
   for (; l < l1; ++l) {
-    const double rup = r[l + 1], sup = sqrt((rup - b) * (rup + b));
-    put(l, 2.0 * (rup + rlo) / (sup + slo));
+    const double rup = r[l + 1], sup = leg(rup);
+    put(l, 2.0 * (rup + rlo) * rcp_d(sup + slo));
     rlo = rup;
     slo = sup;
   }
@@ -106,7 +113,7 @@ __host__ __device__ constexpr int path_ld(int Lp) { return Lp + 1; }
 
 // Bound by latency (one workgroup per sample): every phase is spread over the threads, the
 // serial recursion reads ahead, and each path-matrix entry is formed once, its transposed
-// copy coming from LDS.  100 layers: one sample 75 -> 25 us, 1024 samples 164 -> 67 us.
+// copy coming from LDS.  100 layers: one sample 75 -> 21 us, 1024 samples 164 -> 56 us.
 template <typename Real>
 __global__ __launch_bounds__(kBlockP) void k_profile(Model m, Work w, const double* __restrict__ params,
                                                     const int32_t* __restrict__ n_layers) {
@@ -122,21 +129,28 @@ __global__ __launch_bounds__(kBlockP) void k_profile(Model m, Work w, const doub
   __shared__ double s_knot_x[kMaxKnots], s_knot_y[kMaxKnots], s_knot_d[kMaxKnots];
   __shared__ int s_badt;
   __shared__ int s_cell[kMaxLayers];
-  __shared__ double s_n[kMaxLayers], s_x[kMaxSpecies];
+  __shared__ double s_n[kMaxLayers], s_x[kMaxSpecies], s_th[kMaxParams];
   __shared__ int s_finite, s_above, s_unbound;
   __shared__ unsigned long long s_runs[3], s_heads[3];   // layer-sum groups: bits of run starts, of group heads
-  extern __shared__ uint32_t s_pm[];   // reduced precision, transmission: path matrix as bf16 hi | lo << 16
+  extern __shared__ double s_dyn[];
+  double *s_tg = s_dyn, *s_pg = s_tg + m.n_t, *s_cg = s_pg + m.n_p;   // table axes
+  // reduced precision, transmission: path matrix as bf16 hi | lo << 16
+  uint32_t* s_pm = reinterpret_cast<uint32_t*>(s_cg + m.n_tc);
 
   // virtual sample b of real sample bs; a clear one (cloudy/clear mixing) has no cloud
   const int bs = real_sample(m, b);
   const bool cloudy = m.has_cloud && !clear_sample(m, b);
-  const double* th = params + (size_t)bs * m.P;
+  const double* th = s_th;
   int L = n_layers ? n_layers[bs] : m.L_max;
   int status = 0;
   if (L < 1 || L > m.L_max) {
     status = kBadLayers;
     L = m.L_max;
   }
+  if (tid < m.P) s_th[tid] = params[(size_t)bs * m.P + tid];
+  if (tid < m.n_t) s_tg[tid] = m.t_grid[tid];
+  if (tid < m.n_tc) s_cg[tid] = m.tc_grid[tid];
+  if (tid >= 256 && tid < 256 + m.n_p) s_pg[tid - 256] = m.logp_grid[tid - 256];
   if (tid == 0) {
     s_finite = 1;
     s_above = 0;
@@ -148,15 +162,14 @@ __global__ __launch_bounds__(kBlockP) void k_profile(Model m, Work w, const doub
   if (tid < m.S) s_x[tid] = exp10(th[m.n_tp + tid]);
   __syncthreads();
   if (!status && !s_finite) status = kNonfinite;
-  double x[kMaxSpecies];
   double sx = 0.0;
-  for (int s = 0; s < m.S; ++s) { x[s] = s_x[s]; sx += x[s]; }
+  for (int s = 0; s < m.S; ++s) sx += s_x[s];
   const double xh2 = (1.0 - sx) / (1.0 + kHeH2);
   const double xhe = kHeH2 * xh2;
   double mu = m.mu_fixed;
   if (!(mu > 0.0)) {
     mu = xh2 * kMH2 + xhe * kMHe;
-    for (int s = 0; s < m.S; ++s) mu += x[s] * m.mass[s];
+    for (int s = 0; s < m.S; ++s) mu += s_x[s] * m.mass[s];
   }
   const double scale = m.has_scale ? th[m.idx_scale] : 1.0;
   // an isolated object retrieves its gravity; its radius at p_ref is sqrt(G M / g) (Eq. 47)
@@ -193,18 +206,14 @@ __global__ __launch_bounds__(kBlockP) void k_profile(Model m, Work w, const doub
     return pchip_eval(s_knot_x, s_knot_y, s_knot_d, m.n_knots, log10p_bar);
   };
 
+  // layer temperatures, and the levels' in emission (one copy of the profiles' code: a
+  // kernel that runs each of its lines once is held up by fetching them)
   int badt = 0;
-  for (int l = tid; l < L; l += kBlockP) {
-    double t = temperature(0.5 * (logp_lev(l) + logp_lev(l + 1)));
-    s_t[l] = t;
+  for (int q = tid; q < L + (m.mode == kEmission ? L + 1 : 0); q += kBlockP) {
+    const bool lev = q >= L;
+    const double t = temperature(lev ? logp_lev(q - L) : 0.5 * (logp_lev(q) + logp_lev(q + 1)));
+    (lev ? s_tl[q - L] : s_t[q]) = t;
     badt |= !(t > 0.0) || !isfinite(t);
-  }
-  if (m.mode == kEmission) {
-    for (int j = tid; j <= L; j += kBlockP) {
-      double t = temperature(logp_lev(j));
-      s_tl[j] = t;
-      badt |= !(t > 0.0) || !isfinite(t);
-    }
   }
   if (badt) atomicOr(&s_badt, 1);
   __syncthreads();
@@ -215,37 +224,45 @@ __global__ __launch_bounds__(kBlockP) void k_profile(Model m, Work w, const doub
 
   // hydrostatics (1/r linear in ln p inside each isothermal layer)
   const double kk = kB / (mu * kMu * g_ref * r_ref * r_ref);
-  const double lpref = log10(m.p_ref / kBar);
+  const double lpref = m.log10_pref;
   for (int l = tid; l < L; l += kBlockP) s_inc[l] = kk * s_t[l] * dlnp;
   for (int j = tid; j <= L; j += kBlockP)
     if (logp_lev(j) > lpref) atomicAdd(&s_above, 1);
   __syncthreads();
-  if (tid == 0 && !status) {
-    const int lref = min(max(s_above - 1, 0), L - 1);
+  if (tid < 64 && !status) {
+    // one wave, every lane the same: the loops then run on scalar registers
+    const int lref = __builtin_amdgcn_readfirstlane(min(max(s_above - 1, 0), L - 1));
+    const int Lu = __builtin_amdgcn_readfirstlane(L);
     const double ln10 = 2.302585092994045684017991454684;
     const double u_ref = 1.0 / r_ref;
-    s_u[lref] = u_ref + kk * s_t[lref] * (logp_lev(lref) - lpref) * ln10;
-    s_u[lref + 1] = u_ref - kk * s_t[lref] * (lpref - logp_lev(lref + 1)) * ln10;
+    double u = u_ref + kk * s_t[lref] * (logp_lev(lref) - lpref) * ln10;
+    s_u[lref] = u;
     // the increments eight at a time: one LDS round trip for eight dependent sums
     constexpr int kAhead = 8;
-    double u = s_u[lref];
-    for (int j0 = lref - 1; j0 >= 0; j0 -= kAhead) {
+    int j = lref - 1;
+#pragma unroll 1
+    for (; j >= kAhead - 1; j -= kAhead) {
       double v[kAhead];
 #pragma unroll
-      for (int k = 0; k < kAhead; ++k) v[k] = s_inc[max(j0 - k, 0)];
+      for (int k = 0; k < kAhead; ++k) v[k] = s_inc[j - k];
 #pragma unroll
-      for (int k = 0; k < kAhead; ++k)
-        if (j0 - k >= 0) s_u[j0 - k] = u = u + v[k];
+      for (int k = 0; k < kAhead; ++k) s_u[j - k] = u = u + v[k];
     }
-    u = s_u[lref + 1];
-    for (int j0 = lref + 1; j0 < L; j0 += kAhead) {
+#pragma unroll 1
+    for (; j >= 0; --j) s_u[j] = u = u + s_inc[j];
+    u = u_ref - kk * s_t[lref] * (lpref - logp_lev(lref + 1)) * ln10;
+    s_u[lref + 1] = u;
+    j = lref + 1;
+#pragma unroll 1
+    for (; j + kAhead <= Lu; j += kAhead) {
       double v[kAhead];
 #pragma unroll
-      for (int k = 0; k < kAhead; ++k) v[k] = s_inc[min(j0 + k, L - 1)];
+      for (int k = 0; k < kAhead; ++k) v[k] = s_inc[j + k];
 #pragma unroll
-      for (int k = 0; k < kAhead; ++k)
-        if (j0 + k < L) s_u[j0 + k + 1] = u = u - v[k];
+      for (int k = 0; k < kAhead; ++k) s_u[j + k + 1] = u = u - v[k];
     }
+#pragma unroll 1
+    for (; j < Lu; ++j) s_u[j + 1] = u = u - s_inc[j];
   }
   __syncthreads();
   if (!status)
@@ -316,9 +333,9 @@ __global__ __launch_bounds__(kBlockP) void k_profile(Model m, Work w, const doub
     const double dr = s_dr[l];
     int it, ip, itc = 0;
     double wt, wp, wtc = 0.0;
-    cell_index(m.t_grid, m.n_t, t, it, wt);
-    cell_index(m.logp_grid, m.n_p, lp_bar, ip, wp);
-    if (m.has_cia) cell_index(m.tc_grid, m.n_tc, t, itc, wtc);
+    cell_index(s_tg, m.n_t, t, it, wt);
+    cell_index(s_pg, m.n_p, lp_bar, ip, wp);
+    if (m.has_cia) cell_index(s_cg, m.n_tc, t, itc, wtc);
     w.cells[(size_t)b * Lp + l] = pack_cells(it, ip, itc);
     s_cell[l] = pack_cells(it, ip, itc);
     rl[0] = Real(wt);
@@ -507,23 +524,24 @@ void launch_layer_classes(const Model& m, const Work& w, int B, hipStream_t st) 
   hipLaunchKernelGGL(k_layer_classes, dim3(1), dim3(kBlockClasses), 0, st, w, B);
 }
 
-// dynamic LDS of the reduced-precision profile kernel: the path matrix
-static size_t profile_lds_bytes(const Model& m) {
-  return m.mode == kTransmission ? (size_t)m.L_pad * path_ld(m.L_pad) * 4 : 0;
+// dynamic LDS of the profile kernel: the table axes and, in reduced precision, the path matrix
+static size_t profile_lds_bytes(const Model& m, bool fp64) {
+  return (size_t)(m.n_t + m.n_p + m.n_tc) * 8 +
+         (m.mode == kTransmission && !fp64 ? (size_t)m.L_pad * path_ld(m.L_pad) * 4 : 0);
 }
 
 hipError_t profile_configure(const Model& m, bool fp64) {
   if (fp64) return hipSuccess;
   return hipFuncSetAttribute((const void*)k_profile<float>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)((size_t)kMaxLayers * path_ld(kMaxLayers) * 4));
+                             (int)((size_t)kMaxLayers * path_ld(kMaxLayers) * 4 + 3 * kMaxAxis * 8));
 }
 
 void launch_profile(const Model& m, const Work& w, int B, const double* params, const int32_t* n_layers,
                     bool fp64, hipStream_t st) {
   if (fp64) {
-    hipLaunchKernelGGL(k_profile<double>, dim3(B), dim3(kBlockP), 0, st, m, w, params, n_layers);
+    hipLaunchKernelGGL(k_profile<double>, dim3(B), dim3(kBlockP), profile_lds_bytes(m, true), st, m, w, params, n_layers);
   } else {
-    hipLaunchKernelGGL(k_profile<float>, dim3(B), dim3(kBlockP), profile_lds_bytes(m), st, m, w, params, n_layers);
+    hipLaunchKernelGGL(k_profile<float>, dim3(B), dim3(kBlockP), profile_lds_bytes(m, false), st, m, w, params, n_layers);
     if (m.cloud_ng)
       hipLaunchKernelGGL(k_cloud_q, dim3((unsigned)((m.n_nu_pad + kBlock - 1) / kBlock), (unsigned)B), dim3(kBlock), 0,
                          st, m, w);
