@@ -497,7 +497,9 @@ __device__ inline void eval_terms_deriv_f16(const LayerCoef<S>& c, const LaneCon
 // a layer group being a run of up to kLsGroup consecutive layers in one table cell
 // (listed by the profile kernel), whose table pairs are fetched once per tile,
 // together with the tile's dtau_bar; lanes hold two wavenumbers, partial sums stay
-// in registers across the tiles and are reduced over the wave once
+// in registers across the tiles and are reduced over the wave once, 16 sums at a time by
+// halving lane exchanges (one store per layer; 14 butterflies of six LDS permutes each
+// before: 1024 samples x 30000 wavenumbers x 100 layers, the gradient call 27.8 -> 26.35 ms)
 
 template <int S, bool CIA, bool NGC>
 __global__ __launch_bounds__(kBlock) void k_layer_sums_mixed(Model m, Work w, Tables tb, AdjWork aw, int B) {
@@ -681,7 +683,7 @@ __global__ __launch_bounds__(kBlock) void k_cloud_spectral(Model m, Work w, AdjW
 // zeros) in the 16-row blocks below the frontier, whose products and sums are skipped.
 // Samples run fastest over the workgroups, so an XCD's workgroups read the same table
 // columns.  24 samples x 30000 wavenumbers x 100 layers x 6 absorbers: the whole FP64
-// gradient call 14.0 -> 4.2 ms (vector products with one LDS and one memory read per FMA,
+// gradient call 14.0 -> 3.5 ms (vector products with one LDS and one memory read per FMA,
 // 14 wave butterflies per layer and tile, and table columns no neighbour shared).
 //
 // TILE = 64 wavenumbers up to 128 padded layers; 32 (lanes 32-63 hold no wavenumber and add

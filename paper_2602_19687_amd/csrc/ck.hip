@@ -432,9 +432,13 @@ __global__ __launch_bounds__(kBlockT) void k_ck_trans(Model m, Work w, Tables tb
 // chord is linear, so its factor e^-tau_c multiplies absorber 0's g-sum).  Per chord
 // row the absorption of absorber s is A_s = sum_g w_g (1 - e^-tau_s,g), and the
 // passes combine it as A (+) A_s = A + A_s - A A_s (= 1 - (1 - A)(1 - A_s), without
-// the cancellation of a thin chord's 1 - product of transmissions), kept in LDS per
-// (bin, row).  One absorber per pass keeps a wave's table loads on 16 contiguous
-// bins of one table row.
+// the cancellation of a thin chord's 1 - product of transmissions), kept in the
+// registers of the lanes that own the rows.  One absorber per pass keeps a wave's table
+// loads on 16 contiguous bins of one table row.  Bound by vector work and the latency of
+// its barrier-separated phases at two workgroups per CU (LDS).  256 samples x 2179 bins x
+// 6 absorbers x 100 layers: 8.5 -> 4.1 ms (every layer fetched its entries again, 48 LDS
+// permutes and 16 read-modify-writes per 32-row block formed and kept the g-sums, and the
+// layer records came by vector loads).
 constexpr int kProdBins = kTileNu / kCkG;   // bins per tile
 
 // 32-row blocks of one of two waves: as mblocks_for, costs KBe - 2 mi
