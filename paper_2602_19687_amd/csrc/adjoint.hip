@@ -1453,14 +1453,26 @@ constexpr int kRedElems = 32, kRedSegs = kBlock / kRedElems;
 
 struct ReduceSizes {
   int sums, path, area, levels;   // elements per sample
+  int quads;                      // path-matrix elements taken four to a thread instead of as `path`
 };
+// A path matrix of at most kRedQuad chunks is added by threads that each walk the chunks of
+// four neighbouring entries (16- or 32-byte loads); by segments, such a batch gave each
+// thread one load and the launch hundreds of thousands of workgroups.  100 layers: 1024
+// samples x 4 chunks 354 -> 60 us, 128 x 4 53 -> 19, 64 (up to 150 layers) x 8 74 -> 52; 24
+// FP64 samples 13 either way.  With more chunks there are few samples, and the split over
+// the segments keeps each thread's chain of loads short (one sample: 12 us).
+constexpr int kRedQuad = 16;
 __host__ __device__ inline ReduceSizes reduce_sizes(const Model& m, int C) {
   const bool parts = m.mode == kTransmission && C > 1;
-  return {m.L_max * n_sums(m.S), parts ? m.L_pad * m.L_pad : 0, parts ? m.L_pad : 0,
-          m.mode == kEmission ? m.L_max + 1 : 0};
+  const int path = parts ? m.L_pad * m.L_pad : 0;
+  return {m.L_max * n_sums(m.S), C > kRedQuad ? path : 0, parts ? m.L_pad : 0, m.mode == kEmission ? m.L_max + 1 : 0,
+          C > kRedQuad ? 0 : path};
+}
+__host__ __device__ inline int reduce_split_blocks(const ReduceSizes& z) {
+  return (z.sums + z.path + z.area + z.levels + kRedElems - 1) / kRedElems;
 }
 __host__ __device__ inline int reduce_blocks(const ReduceSizes& z) {
-  return (z.sums + z.path + z.area + z.levels + kRedElems - 1) / kRedElems;
+  return reduce_split_blocks(z) + (z.quads + 4 * kBlock - 1) / (4 * kBlock);
 }
 
 template <typename PbarT>
@@ -1471,8 +1483,35 @@ __global__ __launch_bounds__(kBlock) void k_reduce_chunks(Model m, Work w, AdjWo
   const int nblk = reduce_blocks(z), b = blockIdx.x / nblk;
   if (w.status[b]) return;
   const int L = w.nlay[b];
+  const int part = blockIdx.x - b * nblk, split = reduce_split_blocks(z);
+  if (part >= split) {
+    // four neighbouring entries of a row (L_pad is a multiple of 16, so never across rows);
+    // those of the fours that straddle the diagonal or L and are not read add up unread
+    typedef PbarT quad_t __attribute__((ext_vector_type(4)));
+    const int e = 4 * ((part - split) * kBlock + (int)threadIdx.x), i = e / Lp, l = e - i * Lp;
+    if (e >= z.quads || l + 3 < i || l >= L) return;
+    quad_t* q = reinterpret_cast<quad_t*>(reinterpret_cast<PbarT*>(aw.pbar) + (size_t)b * C * Lp * Lp + e);
+    const size_t step = (size_t)Lp * Lp / 4;
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int c0 = 0; c0 < C; c0 += 4) {
+      quad_t x[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) x[u] = q[min(c0 + u, C - 1) * step];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (c0 + u < C) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) v[k] += (double)x[u][k];
+        }
+    }
+    quad_t sum;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) sum[k] = (PbarT)v[k];
+    *q = sum;
+    return;
+  }
   const int el = threadIdx.x & (kRedElems - 1), seg = threadIdx.x / kRedElems;
-  int e = (blockIdx.x - b * nblk) * kRedElems + el;
+  int e = part * kRedElems + el;
   // where the element's chunks lie: type, first, stride (elements), number
   const PbarT* src = nullptr;
   const double* src64 = nullptr;
