@@ -299,8 +299,11 @@ __device__ inline double rsq_d(double x) {
   r = fma(r, fma(-h * r, r, 0.5), r);
   return fma(r, fma(-h * r, r, 0.5), r);
 }
-// 2^x for finite x (0 or infinity past the exponent range)
+// 2^x (0 or infinity past the exponent range).  The clamp serves x = -inf, the exponent of
+// an absorber whose mixing ratio underflows to zero or whose table holds the lowest double:
+// x - rint(x) would be a NaN there.  Below -1100 2^x is zero.
 __device__ inline double exp2_d(double x) {
+  x = __builtin_fmax(x, -1100.0);
   const double n = __builtin_rint(x), f = x - n;
   return __builtin_ldexp(fma(exp2_q(f), f, 1.0), (int)n);
 }
