@@ -805,8 +805,9 @@ __global__ __launch_bounds__(kBlockT) void k_trans_adj_fp64(Model m, Work w, Tab
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int i = 16 * mi + h + 4 * e;
-          const double tau = acc[e], ex = exp_neg_d(tau);
-          abar_acc[q][e] = fma(dbar, 1.0 - ex, abar_acc[q][e]);
+          double om, ex;
+          absorb_d(acc[e], om, ex);   // a thin chord's om to its last digits: abar sums nothing larger
+          abar_acc[q][e] = fma(dbar, om, abar_acc[q][e]);
           s_tb[i * ld + 16 * nb + n16] = dbar * s_area[i] * ex;
           live |= !(ex == 0.0);
         }

@@ -320,6 +320,37 @@ __device__ inline double rcp_d(double x) {
   r = fma(fma(-x, r, 1.0), r, r);
   return fma(fma(-x, r, 1.0), r, r);
 }
+// e = e^y and em1 = e^y - 1, which keeps its digits where y is small, for -760 <= y <= 709:
+// y = n ln 2 + r with ln 2 in two parts (the first product's difference is exact, Cody and
+// Waite), em1 = 2^n (r + r^2 h(r)) + (2^n - 1) with h = (e^r - 1 - r) / r^2 interpolated at
+// the Chebyshev points of [-ln 2 / 2, ln 2 / 2] (to 2e-18).  Both within an ulp (em1 two for
+// y in [0.35, 1.04]), as the library's.  As 2^(y log2 e) they would carry the rounding of
+// the product: e^-30 to 25 ulp.
+__device__ inline void exp_d(double y, double& em1, double& e) {
+  const double n = __builtin_rint(y * 1.4426950408889634074);
+  double r = fma(n, -0.6931471805599453, y);
+  r = fma(n, -2.3190468138462996e-17, r);
+  double h = 2.0914679376583935e-09;
+  h = fma(h, r, 2.510520637395701e-08);
+  h = fma(h, r, 2.7557273661348637e-07);
+  h = fma(h, r, 2.7557255425746435e-06);
+  h = fma(h, r, 2.4801587325533363e-05);
+  h = fma(h, r, 0.00019841269874800493);
+  h = fma(h, r, 0.0013888888888883752);
+  h = fma(h, r, 0.008333333333326141);
+  h = fma(h, r, 0.04166666666666667);
+  h = fma(h, r, 0.1666666666666667);
+  h = fma(h, r, 0.5);
+  const double t = fma(r * r, h, r), s = __builtin_ldexp(1.0, (int)n);
+  em1 = fma(s, t, s - 1.0);
+  e = fma(s, t, s);
+}
+// e = e^-tau (0 past 745) and om = 1 - e^-tau for tau >= 0 (infinite included; a NaN stays one)
+__device__ inline void absorb_d(double tau, double& om, double& e) {
+  double em1;
+  exp_d(tau > 760.0 ? -760.0 : -tau, em1, e);
+  om = -em1;
+}
 // e^-tau for tau >= 0 (infinite included; a NaN stays one)
 __device__ inline double exp_neg_d(double tau) {
   const double x = -1.4426950408889634074 * tau;

@@ -298,10 +298,9 @@ __global__ __launch_bounds__(kBlockT) void k_trans_fwd_mixed(Model m, Work w, Ta
 // keeping the table entries of a cell while the cell is unchanged, into LDS [layer][nu]; the
 // chords then run on the FP64 matrix unit (wave wv: 16-column block wv & 3, a cost-balanced
 // half of the 16-row blocks), beside the other workgroup's vector work.
-// 1 - e^-tau is formed as such: its absolute rounding, 1e-16 of an annulus, is below the
-// rounding of the opaque core it is added to.  64 samples x 30000 wavenumbers x 100 layers
-// x 6 absorbers: 9.85 -> 2.06 ms (the vector chord waited on one LDS and one scalar load
-// per FMA, and every layer fetched its 28 table entries again).
+// 64 samples x 30000 wavenumbers x 100 layers x 6 absorbers: 9.85 -> 2.06 ms (the vector
+// chord waited on one LDS and one scalar load per FMA, and every layer fetched its 28 table
+// entries again).
 constexpr int kLd64 = kTile64 + 2;   // LDS row length: 16 rows x 2 columns fall on different banks
 
 template <int S, bool CIA>
@@ -366,8 +365,9 @@ __global__ __launch_bounds__(kBlockT) void k_trans_fwd_fp64(Model m, Work w, Tab
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const double tau = acc[e];
-      dsum = fma(area[16 * mi + h + 4 * e], 1.0 - exp_neg_d(tau), dsum);
+      double om, ex;
+      absorb_d(acc[e], om, ex);
+      dsum = fma(area[16 * mi + h + 4 * e], om, dsum);
     }
   }
   dsum += __shfl_xor(dsum, 16);

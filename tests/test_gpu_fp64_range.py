@@ -8,6 +8,7 @@ import numpy as np
 import pytest
 
 import oracle
+import oracle.model
 from parity_util import reduced, rel_err
 
 pytestmark = pytest.mark.gpu
@@ -50,3 +51,24 @@ def test_absorber_without_absorption(cid, n_tp, what):
         # (the derivative by an underflowed X itself is 0 / 0)
         keep = wl["params"][b] > -400.0
         assert _grad_err(g[b][keep], gref[keep]) < 1e-8
+
+
+def test_gradient_of_a_thin_atmosphere(monkeypatch):
+    """Slant optical depths near 1e-18, where 1 - e^-tau formed by subtraction is zero: the
+    temperature moves such a spectrum through the annulus areas and the optical depths in
+    equal parts.  p_ref is the bottom pressure, so the opaque core does not move."""
+    def transit_depth(pm, dtau, r_lev, r_s):
+        return (r_lev[0] ** 2 - (r_lev[1:] ** 2 - r_lev[:-1] ** 2) @ np.expm1(-(pm @ dtau))) / r_s ** 2
+
+    monkeypatch.setattr(oracle.model, "transit_depth", transit_depth)
+    wl = reduced(0, n_nu=200, n_bins=10, batch=1, n_layers=40, step=9)
+    wl.update(p_ref_bar=wl["p_bot"], rayleigh=False, ray_h2=0.0, ray_he=0.0)
+    wl["params"][0] = [1200.0, -27.0]
+    print("[gpu] FP64 gradient of a thin atmosphere", flush=True)
+    fm = _model(wl, 1)
+    _, g, st, _ = fm.grad(torch.tensor(wl["params"], dtype=torch.float64, device="cuda"))
+    g = g.cpu().numpy()[0]
+    fm.close()
+    assert int(st[0]) == 0
+    # both components to the same relative accuracy, whatever their sizes
+    assert rel_err(g, oracle.grad_complex_step(wl, wl["params"][0])) < 1e-8
