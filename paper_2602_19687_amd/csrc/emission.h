@@ -45,20 +45,19 @@ __device__ inline void slab_terms(float x, float e, float& om, float& src) {
   }
 }
 
-// ---- plain FP64 forms (opacity.h: exp2m1_d, rcp_d)
-// Planck intensity 2 h c^2 nu^3 / (e^y - 1), y = h c nu / k T, from c1n3 = 2 h c^2 nu^3 and
-// y2 = y log2(e); em1 returns e^y - 1
-__device__ inline double planck_d(double c1n3, double y2, double& em1) {
+// ---- plain FP64 forms (opacity.h: exp_d, rcp_d, div_d)
+// Planck intensity 2 h c^2 nu^3 / (e^y - 1), y = h c nu / k T, from c1n3 = 2 h c^2 nu^3 (zero
+// past e^709); em1 returns e^y - 1 and ie its reciprocal
+__device__ inline double planck_d(double c1n3, double y, double& em1, double& ie) {
   double e;
-  exp2m1_d(fmin(y2, 1000.0), em1, e);   // past 2^1000 the intensity is zero beside any other
-  return c1n3 * rcp_d(em1);
+  exp_d(fmin(y, 709.0), em1, e);
+  ie = rcp_d(em1);
+  return y > 709.0 ? 0.0 : div_d(c1n3, em1, ie);
 }
 // e = e^-x, om = 1 - e^-x and src = (1 - e^-x)/x - e^-x, by its series below x = 1e-4, for
 // x >= 0; r = 1 / x (unused below 1e-4)
 __device__ inline void slab_d(double x, double& e, double& om, double& src, double& r) {
-  double em1;
-  exp2m1_d(fmax(-1.4426950408889634074 * x, -1000.0), em1, e);
-  om = -em1;
+  absorb_d(x, om, e);
   r = rcp_d(x);
   src = x < 1.0e-4 ? x * (0.5 + x * (-1.0 / 3.0 + x * (0.125 + x * (-1.0 / 30.0)))) : fma(om, r, -e);
 }

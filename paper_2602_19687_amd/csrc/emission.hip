@@ -44,7 +44,7 @@ __global__ __launch_bounds__(kBlock) void k_emission_fp64(Model m, Work w, Table
   const int nu = nu0 + lane;
   const double nud = m.nu[nu];
   const double c1n3 = 2.0 * kHpl * kC * kC * nud * nud * nud;
-  const double c2n = kHpl * kC / kB * 1.4426950408889634074 * nud;
+  const double c2n = kHpl * kC / kB * nud;
   double inv_mu[kAngles], inten[kAngles], bb = 0.0;
 #pragma unroll
   for (int q = 0; q < kAngles; ++q) {
@@ -69,8 +69,8 @@ __global__ __launch_bounds__(kBlock) void k_emission_fp64(Model m, Work w, Table
       if (dtau_out) __builtin_nontemporal_store(d, &dtau_out[((size_t)b * Lp + l) * m.n_nu_pad + nu]);
     }
     for (int j = wv; j <= n; j += kWaves) {
-      double em1;
-      s_b[j][lane] = planck_d(c1n3, c2n / t_lev[c0 + j], em1);
+      double em1, ie;
+      s_b[j][lane] = planck_d(c1n3, c2n / t_lev[c0 + j], em1, ie);
     }
     __syncthreads();
     if (c0 == 0) {

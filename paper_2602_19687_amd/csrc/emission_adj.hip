@@ -281,10 +281,11 @@ __global__ __launch_bounds__(kBlock) void k_emis_adj_fp64(Model m, Work w, AdjWo
   }
   const double c1n3 = 2.0 * kHpl * kC * kC * nd * nd * nd, c2n = kHpl * kC / kB * nd;
   auto planck_at = [&](int j, double& dbdt) {
-    double em1;
-    const double inv_t = rcp_d(t_lev[j]), y = c2n * inv_t;
-    const double bv = planck_d(c1n3, 1.4426950408889634074 * y, em1);
-    dbdt = bv * y * (1.0 + rcp_d(em1)) * inv_t;   // B y e^y / ((e^y - 1) T)
+    double em1, ie;
+    const double t = t_lev[j], inv_t = rcp_d(t), y = div_d(c2n, t, inv_t);
+    const double bv = planck_d(c1n3, y, em1, ie);
+    // B y e^y / ((e^y - 1) T)
+    dbdt = div_d(div_d(bv * y * (em1 + 1.0), em1, ie), t, inv_t);
     return bv;
   };
   const int n_mu = m.n_mu;
@@ -319,9 +320,9 @@ __global__ __launch_bounds__(kBlock) void k_emis_adj_fp64(Model m, Work w, AdjWo
       const double x = d * inv_mu[k];
       double e, om, src, r;
       slab_d(x, e, om, src, r);
-      // d src / dx, by its series for thin slabs
+      // d src / dx = e - src / x, by its series for thin slabs
       const double dsrc = x < 1.0e-3 ? 0.5 + x * (-2.0 / 3.0 + x * (0.375 + x * (-2.0 / 15.0 + x * (5.0 / 144.0))))
-                                     : fma(e, r, e) - om * r * r;
+                                     : fma(-src, r, e);
       const double ib = ibar_top[k] * exp_neg_d(x_above * inv_mu[k]);
       dsum = fma(ib * fma(b_top - inten[k], e, db * dsrc), inv_mu[k], dsum);
       bt_bar = fma(ib, om - src, bt_bar);

@@ -307,18 +307,16 @@ __device__ inline double exp2_d(double x) {
   const double n = __builtin_rint(x), f = x - n;
   return __builtin_ldexp(fma(exp2_q(f), f, 1.0), (int)n);
 }
-// e = 2^x and em1 = 2^x - 1, which keeps its digits where x is small, for |x| <= 1022
-__device__ inline void exp2m1_d(double x, double& em1, double& e) {
-  const double n = __builtin_rint(x), f = x - n;
-  const double t = f * exp2_q(f), s = __builtin_ldexp(1.0, (int)n);
-  em1 = fma(s, t, s - 1.0);
-  e = fma(s, t, s);
-}
-// 1 / x to the last digit or two (x and 1 / x normal): two Newton steps
+// 1 / x (x and 1 / x normal): two Newton steps, the last of which rounds once (0.5 ulp)
 __device__ inline double rcp_d(double x) {
   double r = __builtin_amdgcn_rcp(x);
   r = fma(fma(-x, r, 1.0), r, r);
   return fma(fma(-x, r, 1.0), r, r);
+}
+// a / b given r = 1 / b, with the quotient's own residual added (0.5 ulp; a r alone 1.4)
+__device__ inline double div_d(double a, double b, double r) {
+  const double q = a * r;
+  return fma(fma(-b, q, a), r, q);
 }
 // e = e^y and em1 = e^y - 1, which keeps its digits where y is small, for -760 <= y <= 709:
 // y = n ln 2 + r with ln 2 in two parts (the first product's difference is exact, Cody and
@@ -351,10 +349,11 @@ __device__ inline void absorb_d(double tau, double& om, double& e) {
   exp_d(tau > 760.0 ? -760.0 : -tau, em1, e);
   om = -em1;
 }
-// e^-tau for tau >= 0 (infinite included; a NaN stays one)
+// e^-tau alone
 __device__ inline double exp_neg_d(double tau) {
-  const double x = -1.4426950408889634074 * tau;
-  return exp2_d(x < -1100.0 ? -1100.0 : x);
+  double om, e;
+  absorb_d(tau, om, e);
+  return e;
 }
 
 // Table entries of one layer at this lane's wavenumber: four bilinear corners (T and log p

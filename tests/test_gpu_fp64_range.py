@@ -72,3 +72,20 @@ def test_gradient_of_a_thin_atmosphere(monkeypatch):
     assert int(st[0]) == 0
     # both components to the same relative accuracy, whatever their sizes
     assert rel_err(g, oracle.grad_complex_step(wl, wl["params"][0])) < 1e-8
+
+
+def test_planck_intensity_of_a_cold_object():
+    """An isothermal object's spectrum is B(T) / B(T_*).  With T and the wavenumbers powers of
+    two, h c nu / k T is one rounded constant times a power of two, for the oracle too, so the
+    intensities agree to their own roundings up to e^-368: 4e-15, some twenty roundings of
+    1.1e-16 on either side.  An exponent rounded once more on the way is off by 2e-14."""
+    wl = reduced(2, n_nu=4, n_bins=1, batch=1, n_layers=40)
+    wl["nu"] = np.array([1024.0, 2048.0, 4096.0, 8192.0])
+    wl.update(tp=0, n_knots=0, t_star=4096.0, params=np.concatenate([[[32.0]], wl["params"][:, 5:]], axis=1))
+    print("[gpu] FP64 Planck intensity of a cold object", flush=True)
+    fm = _model(wl, 1)
+    spec, _, st = fm.forward(torch.tensor(wl["params"], dtype=torch.float64, device="cuda"))
+    spec = spec.cpu().numpy()[0]
+    fm.close()
+    assert int(st[0]) == 0
+    assert rel_err(spec, oracle.forward(wl, wl["params"][0])["spectrum"]) < 4e-15
