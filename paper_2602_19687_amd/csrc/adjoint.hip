@@ -965,9 +965,10 @@ constexpr int kBlockC = 512, kWavesC = kBlockC / 64;
 // the layer's levels
 __device__ inline void path_derivs(double bb, double rlo, double rup, double& d_lo, double& d_up, double& d_b) {
   const double xu = (rup - bb) * (rup + bb), xl = (rlo - bb) * (rlo + bb);
-  const double iup = rsq_d(xu), ilo = rsq_d(xl);
-  const double iden = rcp_d(fma(xu, iup, xl * ilo));
-  const double f = 2.0 * (rup + rlo) * iden * iden;
+  double hu, hl;
+  const double sup = sqrt_d(xu, hu), slo = sqrt_d(xl, hl), den = sup + slo;
+  const double iup = rcp_of_root_d(sup, hu), ilo = rcp_of_root_d(slo, hl), iden = rcp_d(den);
+  const double f = div_d(div_d(2.0 * (rup + rlo), den, iden), den, iden);
   d_up = fma(-f * rup, iup, 2.0 * iden);
   d_lo = fma(-f * rlo, ilo, 2.0 * iden);
   d_b = f * bb * (iup + ilo);

@@ -292,12 +292,20 @@ __device__ inline double exp2_q(double f) {
   q = fma(q, f, 0.24022650695910097);
   return fma(q, f, 0.6931471805599453);
 }
-// 1 / sqrt(x) to the last digit or two (x > 0 normal): two Newton steps
-__device__ inline double rsq_d(double x) {
-  double r = __builtin_amdgcn_rsq(x);
-  const double h = 0.5 * x;
-  r = fma(r, fma(-h * r, r, 0.5), r);
-  return fma(r, fma(-h * r, r, 0.5), r);
+// sqrt(x), correctly rounded but for the rarest ties, and half = 1 / (2 sqrt(x)) to 1e-13 (x
+// > 0 normal): one coupled Newton step, then the root's own residual
+__device__ inline double sqrt_d(double x, double& half) {
+  const double r = __builtin_amdgcn_rsq(x);
+  double g = x * r, h = 0.5 * r;
+  const double d = fma(-h, g, 0.5);
+  g = fma(g, d, g);
+  half = h = fma(h, d, h);
+  return fma(fma(-g, g, x), h, g);
+}
+// 1 / s from half = 1 / (2 s) to 1e-13 (0.5 ulp)
+__device__ inline double rcp_of_root_d(double s, double half) {
+  const double r = half + half;
+  return fma(fma(-s, r, 1.0), r, r);
 }
 // 2^x (0 or infinity past the exponent range).  The clamp serves x = -inf, the exponent of
 // an absorber whose mixing ratio underflows to zero or whose table holds the lowest double:

@@ -85,8 +85,8 @@ __device__ inline void path_entries(const double* r, const double* dr, int i, in
   const double b = 0.5 * (r[i] + r[i + 1]);
   // sqrt(r^2 - b^2)
   auto leg = [&](double rl) {
-    const double x = (rl - b) * (rl + b);
-    return x * rsq_d(x);
+    double half;
+    return sqrt_d((rl - b) * (rl + b), half);
   };
   int l = l0;
   if (l == i) {
@@ -99,7 +99,8 @@ __device__ inline void path_entries(const double* r, const double* dr, int i, in
 #pragma unroll 1
   for (; l < l1; ++l) {
     const double rup = r[l + 1], sup = leg(rup);
-    put(l, 2.0 * (rup + rlo) * rcp_d(sup + slo));
+    const double den = sup + slo;
+    put(l, div_d(2.0 * (rup + rlo), den, rcp_d(den)));
     rlo = rup;
     slo = sup;
   }
