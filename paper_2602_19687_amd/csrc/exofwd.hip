@@ -437,8 +437,9 @@ exofwd_status exofwd_create(const exofwd_config* cfg, exofwd_ctx** out) {
   m.t_star = g.t_star;
   m.dilution = g.dilution;
   m.err_c = g.err_c;
-  m.ray_h2 = g.ray_h2;
-  m.ray_he = g.ray_he;
+  // zero without Rayleigh scattering: the gradient's composition terms use them as they are
+  m.ray_h2 = m.has_ray ? g.ray_h2 : 0.0;
+  m.ray_he = m.has_ray ? g.ray_he : 0.0;
   for (int s = 0; s < m.S; ++s) m.mass[s] = g.species_mass ? g.species_mass[s] : 0.0;
   if (m.n_mu > 0) {
     double x[kMaxMu], wg[kMaxMu];

@@ -89,3 +89,18 @@ def test_planck_intensity_of_a_cold_object():
     fm.close()
     assert int(st[0]) == 0
     assert rel_err(spec, oracle.forward(wl, wl["params"][0])["spectrum"]) < 4e-15
+
+
+def test_gradient_without_rayleigh():
+    """Rayleigh scattering switched off with its coefficients left set: no term of it reaches
+    the gradient through the H2 and He mixing ratios."""
+    wl = reduced(0, n_nu=200, n_bins=10, batch=1, n_layers=40, step=9)
+    wl["rayleigh"] = False
+    wl["params"][0] = [1200.0, -8.0]
+    print("[gpu] FP64 gradient without Rayleigh", flush=True)
+    fm = _model(wl, 1)
+    _, g, st, _ = fm.grad(torch.tensor(wl["params"], dtype=torch.float64, device="cuda"))
+    g = g.cpu().numpy()[0]
+    fm.close()
+    assert int(st[0]) == 0
+    assert rel_err(g, oracle.grad_complex_step(wl, wl["params"][0])) < 1e-8
