@@ -459,9 +459,11 @@ __device__ inline float fma_f16hi(float a, half2_t h, float c) {
   return d;
 }
 
-// Line terms of one layer (and its CIA terms) for two wavenumbers with the
-// derivative of each exponent with respect to the T weight: the arithmetic of
-// eval_terms_deriv, with the line pairs entering their FMAs as FP16 operands
+// Line and CIA terms of one layer for two wavenumbers together with the derivative of each
+// exponent with respect to the T weight, from the two log p-interpolated rows u0 (at iT) and
+// u1 (at iT+1), both offset by c + lam:
+//   exponent = u0 + wT (u1 - u0),  d exponent / d wT = u1 - u0.
+// The line pairs enter their FMAs as FP16 operands.
 template <int S, bool CIA>
 __device__ inline void eval_terms_deriv_f16(const LayerCoef<S>& c, const LaneConst<S>& k, const LayerRaw<S, CIA>& r,
                                             float* t0, float* t1, float* dw0, float* dw1) {

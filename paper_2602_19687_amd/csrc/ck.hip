@@ -45,21 +45,6 @@ constexpr int kDppQuadMirror = 0x1B;   // [3,2,1,0]
 constexpr int kDppQuadPrev = 0x90;     // [0,0,1,2]
 constexpr int dpp_quad_lane(int j) { return j * 0x55; }   // lane j of the quad to all four
 
-template <int CTRL>
-__device__ inline uint32_t dpp_u(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, true);
-}
-template <int CTRL>
-__device__ inline float dpp_f(float v) {
-  return __uint_as_float(dpp_u<CTRL>(__float_as_uint(v)));
-}
-template <int CTRL>
-__device__ inline double dpp_d(double v) {
-  const uint64_t u = (uint64_t)__double_as_longlong(v);
-  const uint64_t lo = dpp_u<CTRL>((uint32_t)u), hi = dpp_u<CTRL>((uint32_t)(u >> 32));
-  return __longlong_as_double((long long)(lo | (hi << 32)));
-}
-
 // the smaller of a and b for z = 0, the larger for z = ~0 (one v_med3_u32)
 __device__ inline uint32_t pick(uint32_t a, uint32_t b, uint32_t z) { return max(min(a, b), min(max(a, b), z)); }
 
@@ -69,7 +54,7 @@ template <int CTRL, bool REV>
 __device__ inline void net_cross(uint32_t (&k)[16], uint32_t z) {
   uint32_t o[16];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) o[r] = dpp_u<CTRL>(k[REV ? 15 - r : r]);
+  for (int r = 0; r < 16; ++r) o[r] = dpp_mov<CTRL>(k[REV ? 15 - r : r]);
 #pragma unroll
   for (int r = 0; r < 16; ++r) k[r] = pick(k[r], o[r], z);
 }
@@ -207,7 +192,7 @@ __global__ __launch_bounds__(kBlock) void k_ck_mix(Model m, Work w, Tables tb, i
   for (int k = 0; k < 4; ++k) pair_code[k] = (uint32_t)(16 * q + 2 * (k ^ q));
   // sum over the quad's lanes below this one
   auto quad_excl = [&](double t) {
-    return fma(dpp_d<dpp_quad_lane(0)>(t), g1, fma(dpp_d<dpp_quad_lane(1)>(t), g2, dpp_d<dpp_quad_lane(2)>(t) * g3));
+    return fma(dpp_mov<dpp_quad_lane(0)>(t), g1, fma(dpp_mov<dpp_quad_lane(1)>(t), g2, dpp_mov<dpp_quad_lane(2)>(t) * g3));
   };
 
   float mix0 = sp0[0], mix1 = sp1[0];   // the running mixture: absorber 0 to start
@@ -216,10 +201,10 @@ __global__ __launch_bounds__(kBlock) void k_ck_mix(Model m, Work w, Tables tb, i
     // rows 2q and 2q + 1 of the pair matrix
     float v[16];
     {
-      const float b0 = dpp_f<dpp_quad_lane(0)>(sp0[s]), b1 = dpp_f<dpp_quad_lane(0)>(sp1[s]);
-      const float b2 = dpp_f<dpp_quad_lane(1)>(sp0[s]), b3 = dpp_f<dpp_quad_lane(1)>(sp1[s]);
-      const float b4 = dpp_f<dpp_quad_lane(2)>(sp0[s]), b5 = dpp_f<dpp_quad_lane(2)>(sp1[s]);
-      const float b6 = dpp_f<dpp_quad_lane(3)>(sp0[s]), b7 = dpp_f<dpp_quad_lane(3)>(sp1[s]);
+      const float b0 = dpp_mov<dpp_quad_lane(0)>(sp0[s]), b1 = dpp_mov<dpp_quad_lane(0)>(sp1[s]);
+      const float b2 = dpp_mov<dpp_quad_lane(1)>(sp0[s]), b3 = dpp_mov<dpp_quad_lane(1)>(sp1[s]);
+      const float b4 = dpp_mov<dpp_quad_lane(2)>(sp0[s]), b5 = dpp_mov<dpp_quad_lane(2)>(sp1[s]);
+      const float b6 = dpp_mov<dpp_quad_lane(3)>(sp0[s]), b7 = dpp_mov<dpp_quad_lane(3)>(sp1[s]);
       const float br[8] = {b0, b1, b2, b3, b4, b5, b6, b7};
 #pragma unroll
       for (int r = 0; r < 8; ++r) {
@@ -300,7 +285,7 @@ __global__ __launch_bounds__(kBlock) void k_ck_mix(Model m, Work w, Tables tb, i
     f0 = fma((double)val_at(a0), x0, f0);
     f1 = fma((double)val_at(a1), x1, f1);
     // interval 2q starts at the previous lane's second edge
-    const double fp = dpp_d<kDppQuadPrev>(f1);
+    const double fp = dpp_mov<kDppQuadPrev>(f1);
     mix0 = (float)((f0 - (q > 0 ? fp : 0.0)) * inv0);
     mix1 = (float)((f1 - f0) * inv1);
   }
@@ -440,19 +425,6 @@ __global__ __launch_bounds__(kBlockT) void k_ck_trans(Model m, Work w, Tables tb
 // permutes and 16 read-modify-writes per 32-row block formed and kept the g-sums, and the
 // layer records came by vector loads).
 constexpr int kProdBins = kTileNu / kCkG;   // bins per tile
-
-// 32-row blocks of one of two waves: as mblocks_for, costs KBe - 2 mi
-__device__ inline unsigned split_blocks32(int part, int MBe, int KBe) {
-  unsigned mine = 0;
-  int c0 = 0, c1 = 0;
-  for (int mi = 0; mi < MBe; ++mi) {
-    const int cost = KBe - 2 * mi;
-    const bool first = c0 <= c1;
-    if (first == (part == 0)) mine |= 1u << mi;
-    (first ? c0 : c1) += cost;
-  }
-  return mine;
-}
 
 template <int S, bool CIA>
 __global__ __launch_bounds__(kBlockT) void k_ck_trans_prod(Model m, Work w, Tables tb, int B,

@@ -267,10 +267,10 @@ exofwd_status exofwd_create(const exofwd_config* cfg, exofwd_ctx** out) {
   if (g.batch_max < 1) return create_fail(E, "batch_max < 1");
   if (g.n_nu < 1 || !g.nu || !ascending(g.nu, g.n_nu) || !(g.nu[0] > 0.0))
     return create_fail(E, "nu must hold n_nu >= 1 positive ascending wavenumbers");
-  if (g.n_t < 2 || g.n_t > 255 || g.n_p < 2 || g.n_p > 255 || !g.t_grid || !g.logp_grid || !g.log10_xsec)
+  if (g.n_t < 2 || g.n_t > kMaxAxis || g.n_p < 2 || g.n_p > kMaxAxis || !g.t_grid || !g.logp_grid || !g.log10_xsec)
     return create_fail(E, "table axes need 2..255 points each and the table pointers");
   if (!ascending(g.t_grid, g.n_t) || !ascending(g.logp_grid, g.n_p)) return create_fail(E, "table axes not ascending");
-  if (g.has_cia && (g.n_tc < 2 || g.n_tc > 255 || !g.tc_grid || !g.log10_cia || !ascending(g.tc_grid, g.n_tc)))
+  if (g.has_cia && (g.n_tc < 2 || g.n_tc > kMaxAxis || !g.tc_grid || !g.log10_cia || !ascending(g.tc_grid, g.n_tc)))
     return create_fail(E, "CIA axis needs 2..255 ascending temperatures and the CIA table");
   if (!(g.mu_fixed > 0.0) && !g.species_mass) return create_fail(E, "species_mass is NULL and mu_fixed <= 0");
   if (g.n_bins < 1 || !g.bin_lo || !g.bin_hi || !g.y_obs || !g.y_err) return create_fail(E, "bins or data missing");

@@ -25,6 +25,24 @@ __device__ inline int class_position(int s, int n_slots, int per_slot) {
   return (s % spx) * 8 + s / spx;
 }
 
+// 32-row blocks of the path matrix of one of two waves that share a column block: each block
+// in turn goes to the wave with the least cost so far; block mi costs its K extent KBe - 2 mi
+__device__ inline unsigned split_blocks32(int part, int MBe, int KBe) {
+  unsigned mine = 0;
+  int c0 = 0, c1 = 0;
+  for (int mi = 0; mi < MBe; ++mi) {
+    const int cost = KBe - 2 * mi;
+    if (c0 <= c1) {
+      if (part == 0) mine |= 1u << mi;
+      c0 += cost;
+    } else {
+      if (part == 1) mine |= 1u << mi;
+      c1 += cost;
+    }
+  }
+  return mine;
+}
+
 // ---- sums over a wave of 16 values per lane at once: the lanes of quad n (n = lane / 4) get
 // the sum of v[n].  Halving exchanges: each step a lane passes on the half of its values
 // that its partner keeps, so the 16 sums take about 40 instructions (FP32) where a
@@ -33,6 +51,14 @@ __device__ inline int class_position(int s, int n_slots, int per_slot) {
 template <int CTRL>
 __device__ inline uint32_t dpp_mov(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, true);
+}
+template <int CTRL>
+__device__ inline float dpp_mov(float v) { return __uint_as_float(dpp_mov<CTRL>(__float_as_uint(v))); }
+template <int CTRL>
+__device__ inline double dpp_mov(double v) {
+  const uint64_t u = (uint64_t)__double_as_longlong(v);
+  const uint64_t lo = dpp_mov<CTRL>((uint32_t)u), hi = dpp_mov<CTRL>((uint32_t)(u >> 32));
+  return __longlong_as_double((long long)(lo | (hi << 32)));
 }
 // the value of lane l ^ BIT (1, 2, 4 or 8)
 template <int BIT>

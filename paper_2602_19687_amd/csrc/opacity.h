@@ -187,59 +187,6 @@ __device__ inline void eval_terms(const LayerCoef<S>& c, const LaneConst<S>& k, 
   }
 }
 
-// Fetch and evaluate in one step.
-template <int S, bool CIA, bool NGC = false>
-__device__ inline void layer_terms(const LayerCoef<S>& c, const LaneConst<S>& k, const TableGeom& g,
-                                   __amdgpu_buffer_rsrc_t rh, __amdgpu_buffer_rsrc_t rhc, uint32_t voff,
-                                   float& d0, float& d1, float q0 = 1.0f, float q1 = 1.0f) {
-  LayerRaw<S, CIA> r;
-  fetch_terms<S, CIA>(c, g, rh, rhc, voff, r);
-  eval_terms<S, CIA, NGC>(c, k, r, d0, d1, q0, q1);
-}
-
-// Line and CIA terms of one layer for two wavenumbers together with the
-// derivative of each exponent with respect to the T weight, from the two
-// log p-interpolated rows u0 (at iT) and u1 (at iT+1), both offset by c + lam:
-//   exponent = u0 + wT (u1 - u0),  d exponent / d wT = u1 - u0.
-template <int S, bool CIA>
-__device__ inline void eval_terms_deriv(const LayerCoef<S>& c, const LaneConst<S>& k, const LayerRaw<S, CIA>& r,
-                                        float* t0, float* t1, float* dw0, float* dw1) {
-#pragma unroll
-  for (int s = 0; s < S; ++s) {
-    const half2_t h00 = r.h[4 * s], h10 = r.h[4 * s + 1], h01 = r.h[4 * s + 2], h11 = r.h[4 * s + 3];
-    const float cl0 = k.c0[s] + c.lam[s], cl1 = k.c1[s] + c.lam[s];
-    const float u00 = fmaf(c.omp, (float)h00.x, fmaf(c.wp, (float)h01.x, cl0));
-    const float u10 = fmaf(c.omp, (float)h10.x, fmaf(c.wp, (float)h11.x, cl0));
-    const float u01 = fmaf(c.omp, (float)h00.y, fmaf(c.wp, (float)h01.y, cl1));
-    const float u11 = fmaf(c.omp, (float)h10.y, fmaf(c.wp, (float)h11.y, cl1));
-    dw0[s] = u10 - u00;
-    dw1[s] = u11 - u01;
-    t0[s] = exp2_fast(fmaf(c.wt, dw0[s], u00));
-    t1[s] = exp2_fast(fmaf(c.wt, dw1[s], u01));
-  }
-  if constexpr (CIA) {
-#pragma unroll
-    for (int p = 0; p < 2; ++p) {
-      const half2_t a = r.h[4 * S + 2 * p], b = r.h[4 * S + 2 * p + 1];
-      const float u0 = (float)a.x + (k.cc0[p] + c.lamc[p]);
-      const float u1 = (float)a.y + (k.cc1[p] + c.lamc[p]);
-      dw0[S + p] = (float)b.x - (float)a.x;
-      dw1[S + p] = (float)b.y - (float)a.y;
-      t0[S + p] = exp2_fast(fmaf(c.wtc, dw0[S + p], u0));
-      t1[S + p] = exp2_fast(fmaf(c.wtc, dw1[S + p], u1));
-    }
-  }
-}
-
-template <int S, bool CIA>
-__device__ inline void layer_terms_deriv(const LayerCoef<S>& c, const LaneConst<S>& k, const TableGeom& g,
-                                         __amdgpu_buffer_rsrc_t rh, __amdgpu_buffer_rsrc_t rhc, uint32_t voff,
-                                         float* t0, float* t1, float* dw0, float* dw1) {
-  LayerRaw<S, CIA> r;
-  fetch_terms<S, CIA>(c, g, rh, rhc, voff, r);
-  eval_terms_deriv<S, CIA>(c, k, r, t0, t1, dw0, dw1);
-}
-
 __device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void* p, size_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)(bytes > 0x7fffffffu ? 0x7fffffff : bytes),
                                            0x00020000);

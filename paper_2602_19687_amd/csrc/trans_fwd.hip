@@ -16,24 +16,6 @@
 
 namespace exofwd {
 
-// Path-matrix A fragments: cost-balanced split of the 32-row blocks between the
-// two waves that share a 32-column block.
-__device__ inline unsigned mblocks_for(int part, int MBe, int KBe) {
-  unsigned mine = 0;
-  int c0 = 0, c1 = 0;
-  for (int mi = 0; mi < MBe; ++mi) {
-    const int cost = KBe - 2 * mi;
-    if (c0 <= c1) {
-      if (part == 0) mine |= 1u << mi;
-      c0 += cost;
-    } else {
-      if (part == 1) mine |= 1u << mi;
-      c1 += cost;
-    }
-  }
-  return mine;
-}
-
 // `cls` (may be null): the layer-count classes of the call (layer_classes), whose class
 // `cl` this launch serves; `lt` is the LDS tile's layer capacity, a multiple of 32: at
 // least every served sample's layers, or with KS (K split) fewer: the layers then pass
@@ -159,7 +141,7 @@ __global__ __launch_bounds__(kBlockT) void k_trans_fwd_mixed(Model m, Work w, Ta
   const int MBe = (L + 31) >> 5;
   const int KB = Lp >> 4;
   const int nb = wv & 3;
-  const unsigned mine = mblocks_for(wv >> 2, MBe, KBe);
+  const unsigned mine = split_blocks32(wv >> 2, MBe, KBe);
   const size_t plane = (size_t)(Lp >> 5) * KB * 512;
   // this sample's P fragments (hi plane, then lo plane): lanes address their 16 bytes
   // with the vector offset, blocks with the scalar offset
