@@ -56,6 +56,11 @@ __host__ __device__ inline double ck_pair_weight(double wa, double wb) {
   return rint(wa * wb * 4503599627370496.0) * 2.220446049250313080847e-16;
 }
 
+// Logarithm that the FP64 kernels read for an opacity that is zero: of a prefactor that
+// underflows (a mixing ratio below 1e-323), and in place of table entries below it.  Any sum
+// of it with others' is finite, and 2 to its power is zero.
+constexpr double kAbsentLog = -1.0e300;
+
 // packed interpolation cells of one layer: iT | iP << 8 | iTc << 16
 __host__ __device__ inline int pack_cells(int it, int ip, int itc) { return it | (ip << 8) | (itc << 16); }
 

@@ -77,6 +77,12 @@ bool upload(T* dst, const T* src, size_t count) {
   return hipMemcpy(dst, src, count * sizeof(T), hipMemcpyHostToDevice) == hipSuccess;
 }
 
+// a row of an FP64 table: entries below kAbsentLog (the lowest double, say) would overflow
+// on the way to log2
+void copy_log_row(double* dst, const double* src, int n) {
+  for (int i = 0; i < n; ++i) dst[i] = std::max(src[i], kAbsentLog);
+}
+
 bool ascending(const double* v, int n) {
   for (int i = 0; i + 1 < n; ++i)
     if (!(v[i + 1] > v[i])) return false;
@@ -483,8 +489,7 @@ exofwd_status exofwd_create(const exofwd_config* cfg, exofwd_ctx** out) {
     std::vector<double> t64((size_t)m.S * rows * np, -1000.0);
     for (int s = 0; s < m.S; ++s)
       for (int r = 0; r < rows; ++r)
-        std::memcpy(&t64[((size_t)s * rows + r) * np], g.log10_xsec + ((size_t)s * rows + r) * g.n_nu,
-                    sizeof(double) * g.n_nu);
+        copy_log_row(&t64[((size_t)s * rows + r) * np], g.log10_xsec + ((size_t)s * rows + r) * g.n_nu, g.n_nu);
     double* d64 = A(dalloc<double>(c, t64.size()));
     double* dn4 = A(dalloc<double>(c, np));
     if (ok) ok = upload(d64, t64.data(), t64.size()) && upload(dn4, nu4.data(), np);
@@ -493,7 +498,7 @@ exofwd_status exofwd_create(const exofwd_config* cfg, exofwd_ctx** out) {
     if (m.has_cia) {
       std::vector<double> c64((size_t)2 * m.n_tc * np, -1000.0);
       for (int r = 0; r < 2 * m.n_tc; ++r)
-        std::memcpy(&c64[(size_t)r * np], g.log10_cia + (size_t)r * g.n_nu, sizeof(double) * g.n_nu);
+        copy_log_row(&c64[(size_t)r * np], g.log10_cia + (size_t)r * g.n_nu, g.n_nu);
       double* dc = A(dalloc<double>(c, c64.size()));
       if (ok) ok = upload(dc, c64.data(), c64.size());
       c->tb.tc64 = dc;

@@ -254,11 +254,9 @@ __device__ inline double rcp_of_root_d(double s, double half) {
   const double r = half + half;
   return fma(fma(-s, r, 1.0), r, r);
 }
-// 2^x (0 or infinity past the exponent range).  The clamp serves x = -inf, the exponent of
-// an absorber whose mixing ratio underflows to zero or whose table holds the lowest double:
-// x - rint(x) would be a NaN there.  Below -1100 2^x is zero.
+// 2^x for finite x (0 or infinity past the exponent range).  At x = -inf, x - rint(x) would
+// be a NaN: the exponents are kept finite where they come from (kAbsentLog).
 __device__ inline double exp2_d(double x) {
-  x = __builtin_fmax(x, -1100.0);
   const double n = __builtin_rint(x), f = x - n;
   return __builtin_ldexp(fma(exp2_q(f), f, 1.0), (int)n);
 }

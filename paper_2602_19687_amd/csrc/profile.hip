@@ -76,6 +76,10 @@ __device__ inline uint16_t bf16_rn(float f) {
 }
 __device__ inline float bf16_to_f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
+// log2 of a prefactor, finite in FP64 also for zero (in FP32 the constant is -inf, whose
+// power the hardware's exponential takes as zero)
+__device__ inline double log2_or_absent(double v) { return v == 0.0 ? kAbsentLog : log2(v); }
+
 // Path matrix entries P_1D[i][l] (Eq. 43), l in [l0, l1), l0 >= i, with b_i the mid radius
 // of layer i: put(l, value).  The l > i case uses
 // sqrt(r_up^2-b^2) - sqrt(r_lo^2-b^2) = dr (r_up+r_lo)/(s_up+s_lo), which has no
@@ -355,8 +359,8 @@ __global__ __launch_bounds__(kBlockP) void k_profile(Model m, Work w, const doub
       dcl = m.kappa_cloud * mu * kMu * n * f * dr;
     }
     rl[4] = Real(dcl);
-    rl[5] = Real(m.has_cia ? log2(n * n * xh2 * xh2 * dr) : -1000.0);
-    rl[6] = Real(m.has_cia ? log2(n * n * xh2 * xhe * dr) : -1000.0);
+    rl[5] = Real(m.has_cia ? log2_or_absent(n * n * xh2 * xh2 * dr) : -1000.0);
+    rl[6] = Real(m.has_cia ? log2_or_absent(n * n * xh2 * xhe * dr) : -1000.0);
     s_n[l] = n;
     area[l] = Real(dr * (s_r[l] + s_r[l + 1]) / (m.r_s * m.r_s));
   }
@@ -366,7 +370,7 @@ __global__ __launch_bounds__(kBlockP) void k_profile(Model m, Work w, const doub
     const int l = e / m.S, s = e - l * m.S;
     Real* rl = rec + (size_t)l * RL;
     const double pre = l < L ? s_n[l] * s_x[s] * s_dr[l] : 0.0;
-    rl[kRecFixed + s] = l < L ? Real(log2(pre)) : Real(-1000);
+    rl[kRecFixed + s] = l < L ? Real(log2_or_absent(pre)) : Real(-1000);
     if (wide) rl[kRecFixed + m.S + s] = Real(pre);
   }
   if (w.lsg) {
