@@ -686,7 +686,11 @@ __global__ __launch_bounds__(kBlock) void k_cloud_spectral(Model m, Work w, AdjW
 // Samples run fastest over the workgroups, so an XCD's workgroups read the same table
 // columns.  24 samples x 30000 wavenumbers x 100 layers x 6 absorbers: the whole FP64
 // gradient call 14.0 -> 3.5 ms (vector products with one LDS and one memory read per FMA,
-// 14 wave butterflies per layer and tile, and table columns no neighbour shared).
+// 14 wave butterflies per layer and tile, and table columns no neighbour shared).  What is
+// left: the accumulators of Pbar and abar stay live beside a cell's table entries and terms
+// in the sums, so the kernel takes all 256 registers (two waves per SIMD) and spills 140 to
+// 648 bytes per lane (456 at six absorbers with CIA); vector instructions issue in 32 % of
+// its cycles.
 //
 // TILE = 64 wavenumbers up to 128 padded layers; 32 (lanes 32-63 hold no wavenumber and add
 // zeros) up to 160, where two 64-wavenumber arrays no longer fit in LDS.
@@ -1464,7 +1468,10 @@ struct ReduceSizes {
 // thread one load and the launch hundreds of thousands of workgroups.  100 layers: 1024
 // samples x 4 chunks 354 -> 60 us, 128 x 4 53 -> 19, 64 (up to 150 layers) x 8 74 -> 52; 24
 // FP64 samples 13 either way.  With more chunks there are few samples, and the split over
-// the segments keeps each thread's chain of loads short (one sample: 12 us).
+// the segments keeps each thread's chain of loads short (one sample: 12 us).  About the line,
+// with the chain, fours against segments: 16 chunks (64 samples) 40 layers 25 us (30), 100
+// layers 34 (52), 160 layers 47 (76); 32 chunks 28 (27), 34 (42), 47 (60); 64 chunks 34 (26),
+// 39 (39), 48 (54): up to 16 the fours are the better for every layer count.
 constexpr int kRedQuad = 16;
 __host__ __device__ inline ReduceSizes reduce_sizes(const Model& m, int C) {
   const bool parts = m.mode == kTransmission && C > 1;
@@ -1598,8 +1605,9 @@ int adjoint_chunks(const Model& m, const AdjWork& aw, int B, bool fp64) {
   if (m.mode == kEmission) return 1;   // the emission reverse pass keeps no per-chunk partials
   const int tiles = m.n_nu_pad / (fp64 ? adj_tile64(m) : adj_tile(aw.variant));
   if (fp64) {
-    // one workgroup per CU at a time: of the splits into at most 1024 work items, the one
-    // whose rounds over the chip take the fewest tiles in a row (the coarsest of equals)
+    // one workgroup per CU at a time (its 256 registers, whatever its LDS): of the splits into
+    // at most 1024 work items, the one whose rounds over the chip take the fewest tiles in a
+    // row (the coarsest of equals)
     const int cus = 256, cmax = std::min(std::max(1024 / B, 1), tiles);
     int best = 1;
     long cost = LONG_MAX;

@@ -18,7 +18,7 @@ namespace exofwd {
 // table entries of a cell kept while the cell is unchanged) and Planck rows, into LDS; each
 // wave then carries its angles up through the chunk.  Chunks keep the LDS at 35 KB, so four
 // workgroups share a CU (one, when whole columns were staged).  24 samples x 20000
-// wavenumbers x 100 layers x 8 absorbers: 3.06 -> 0.90 ms; bound by the FP64 vector rate.
+// wavenumbers x 100 layers x 8 absorbers: 3.06 -> 0.86 ms; bound by the FP64 vector rate.
 constexpr int kChunk64 = 32;
 
 template <int S, bool CIA>

@@ -253,9 +253,9 @@ __global__ __launch_bounds__(kBlock) void k_layer_sums_emis(Model m, Work w, Tab
 // ============================================================================
 // plain FP64 emission adjoint: the same two passes and sums in double, from the
 // FP64 forward's stored layer optical depths and the FP64 log10 sigma tables.  24 samples
-// x 20000 wavenumbers x 100 layers x 8 absorbers x 4 angles: sweeps 1.57 -> 0.85 ms (one
+// x 20000 wavenumbers x 100 layers x 8 absorbers x 4 angles: sweeps 1.57 -> 0.81 ms (one
 // reciprocal for the three quotients of a slab, lane moves for the level sums, the next
-// layer's loads in flight), layer sums 2.66 -> 0.71 ms (sums in registers, entries fetched
+// layer's loads in flight), layer sums 2.66 -> 0.65 ms (sums in registers, entries fetched
 // once per cell and tile; the accumulators used to live in scratch memory)
 __global__ __launch_bounds__(kBlock) void k_emis_adj_fp64(Model m, Work w, AdjWork aw, int B) {
   const int logical = xcd_logical_block(blockIdx.x, gridDim.x);

@@ -8,7 +8,9 @@
 // from kSplitLL wavenumbers on (they pass through the d lnL / d m_k buffer); below, in the
 // sample's workgroup, where another launch would cost more than it gives.  Measured, both
 // kernels against one: 1 sample x 30000 wavenumbers 11 us (26), 64 x 400000 59 (222), 1024 x
-// 30000 91 (120); 1 x 2000 in one kernel 5.7.
+// 30000 91 (120); 1 x 2000 in one kernel 5.7.  About the line, whole calls on 2 layers, split
+// against not (1, 256 and 1024 samples): 2000 wavenumbers 23.2 us (20.8), 40.9 (37.7), 110.5
+// (109.0); 4096 23.3 (23.4), 55.8 (54.7), 182 (182); 8192 23.7 (27.5), 86.8 (88.3), 332 (333).
 #include "kernels.h"
 
 #include <type_traits>
@@ -135,7 +137,7 @@ __global__ __launch_bounds__(kBlockLL) void k_loglike(Model m, Work w, const dou
     }
     mpart += r / s2 * (mix ? f * m_cld + (1.0 - f) * m_cf : m_cld);
   }
-  // sums over the block in a fixed order: each wave's butterfly, then the 16 waves
+  // sums over the block in a fixed order: each wave's butterfly, then the waves
   part = wave_sum_all(part);
   fpart = wave_sum_all(fpart);
   mpart = wave_sum_all(mpart);

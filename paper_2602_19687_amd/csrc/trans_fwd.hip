@@ -280,7 +280,7 @@ __global__ __launch_bounds__(kBlockT) void k_trans_fwd_mixed(Model m, Work w, Ta
 // keeping the table entries of a cell while the cell is unchanged, into LDS [layer][nu]; the
 // chords then run on the FP64 matrix unit (wave wv: 16-column block wv & 3, a cost-balanced
 // half of the 16-row blocks), beside the other workgroup's vector work.
-// 64 samples x 30000 wavenumbers x 100 layers x 6 absorbers: 9.85 -> 2.06 ms (the vector
+// 64 samples x 30000 wavenumbers x 100 layers x 6 absorbers: 9.85 -> 2.07 ms (the vector
 // chord waited on one LDS and one scalar load per FMA, and every layer fetched its 28 table
 // entries again).
 constexpr int kLd64 = kTile64 + 2;   // LDS row length: 16 rows x 2 columns fall on different banks
