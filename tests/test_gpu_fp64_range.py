@@ -53,6 +53,23 @@ def test_absorber_without_absorption(cid, n_tp, what):
         assert _grad_err(g[b][keep], gref[keep]) < 1e-8
 
 
+@pytest.mark.parametrize("cid,n_tp", [(3, 3), (2, 5)], ids=["trans", "emis"])
+def test_mixing_ratio_that_underflows_in_reduced_precision(cid, n_tp):
+    """The reduced-precision record of a zero prefactor (a logarithm of -inf) adds nothing
+    either: spectra to the 1e-3 of that path."""
+    from paper_2602_19687_amd import ForwardModel
+    wl = reduced(cid, n_nu=130, n_bins=7, batch=1, n_layers=40, step=97)
+    wl["params"][0, n_tp + 1] = -400.0
+    print(f"[gpu] reduced precision, underflowing mixing ratio cid={cid}", flush=True)
+    fm = ForwardModel(wl, precision="mixed", batch_max=1)
+    spec, lnl, st = fm.forward(torch.tensor(wl["params"], dtype=torch.float64, device="cuda"))
+    spec = spec.double().cpu().numpy()
+    fm.close()
+    ref = oracle.forward(wl, wl["params"][0])
+    assert int(st[0]) == 0 and rel_err(spec[0], ref["spectrum"]) < 1e-3
+    assert abs(float(lnl[0]) - ref["lnL"]) <= 1e-3 * abs(ref["lnL"])
+
+
 def test_gradient_of_a_thin_atmosphere(monkeypatch):
     """Slant optical depths near 1e-18, where 1 - e^-tau formed by subtraction is zero: the
     temperature moves such a spectrum through the annulus areas and the optical depths in
